@@ -1,7 +1,7 @@
 // Cache population kernels: RoPE at absolute positions (Eq. 3), KIVI
 // quantisation of cached chunks (Sec. 4.5, Eq. 7) and the chunks' importance
 // for the eviction order (Sec. 4.4).  These prepare the chunk pool and the
-// probe-pass tensors; they are not timed as part of the path.
+// probe-pass tensors: every chunk a request did not find goes through them.
 #include <math.h>
 
 #include "kvb_device.h"
@@ -75,129 +75,196 @@ rope_rows_kernel(int64_t n_outer, int64_t n_rows, int64_t n_inner, const float* 
   }
 }
 
-template <typename T>
-__device__ __forceinline__ double load_d(const void* p, int64_t i) {
-  return (double)reinterpret_cast<const T*>(p)[i];
+// Code of x in a group with minimum mn and range r:
+//   c = clamp(rint(((x - mn) / r) * levels), 0, levels), 0 for a constant group.
+// The double division is replaced by a product with inv = 1 / r wherever that
+// cannot change c: both forms carry at most three roundings of a value of at
+// most `levels` (255), so they differ by less than 1e-12, and rint can only
+// tell them apart within that distance of a half.  A value closer than 1e-9 to
+// a half, or not a number, takes the division; so does a range whose
+// reciprocal leaves the normal numbers (`fast` false).  r == 0 is never fast.
+__device__ __forceinline__ uint32_t quant_code(double x, double mn, double r, double inv, bool fast,
+                                               double levels) {
+  const double a = x - mn;
+  double t = (a * inv) * levels;
+  double c = rint(t);
+  if (__builtin_expect(!fast || !(fabs(t - c) < 0.5 - 1e-9), 0)) {
+    t = r != 0.0 ? (a / r) * levels : 0.0;
+    c = rint(t);
+  }
+  return (uint32_t)fmin(fmax(c, 0.0), levels);
+}
+__device__ __forceinline__ bool quant_fast(double r) { return r > 1e-290 && r < 1e290; }
+
+// N consecutive elements at p (16-byte aligned for N * sizeof(T) >= 16)
+template <typename T, int N>
+__device__ __forceinline__ void load_n(const T* p, T (&x)[N]) {
+  typedef __attribute__((ext_vector_type(N * sizeof(T) >= 16 ? 16 / (int)sizeof(T) : N))) T V;
+  constexpr int E = sizeof(V) / sizeof(T);
+#pragma unroll
+  for (int i = 0; i < N / E; ++i) {
+    const V v = reinterpret_cast<const V*>(p)[i];
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[i * E + e] = v[e];
+  }
 }
 
-// Keys: one thread per (slot, layer, head, token group, channel pair).
-template <typename T>
-__global__ void __launch_bounds__(256)
-quant_keys_kernel(int32_t n_pool, int32_t L, int32_t first_layer, int32_t n_in, int32_t Hkv,
-                  int32_t C, int32_t D, int32_t bits, int32_t Gk, const void* __restrict__ in,
-                  uint8_t* __restrict__ codes, float* __restrict__ scale,
-                  float* __restrict__ zero) {
-  const int64_t pairs = D / 2;
-  const int64_t n_groups = C / Gk;
-  const int64_t total = (int64_t)n_pool * n_in * Hkv * n_groups * pairs;
-  const double levels = (double)((1 << bits) - 1);
-  const int cb = D * bits / 8;
-  for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total;
-       w += (int64_t)gridDim.x * blockDim.x) {
-    const int j0 = (int)(w % pairs) * 2;
-    int64_t rest = w / pairs;
-    const int g = (int)(rest % n_groups);
-    rest /= n_groups;
-    const int h = (int)(rest % Hkv);
-    rest /= Hkv;
-    const int li = (int)(rest % n_in);
-    const int64_t p = rest / n_in;
-    const int l = first_layer + li;
-    const int64_t in_base = (((p * n_in + li) * Hkv + h) * C) * (int64_t)D;
-    const int64_t out_row = ((p * L + l) * Hkv + h) * (int64_t)C;
-    double mn[2], mx[2];
-    for (int e = 0; e < 2; ++e) {
-      mn[e] = INFINITY;
-      mx[e] = -INFINITY;
-    }
-    for (int u = g * Gk; u < (g + 1) * Gk; ++u)
+// Keys: one workgroup of 2 D threads per (slot, layer, head) slab; a thread
+// owns one channel pair of 32 consecutive tokens, so a row is read by adjacent
+// lanes, and holds them in registers: the input is read once, every load in
+// flight together.  HBM-bound on the input.  Groups of 64 or 128 tokens meet
+// through LDS; smaller ones (SMALL) are found among the thread's own quads.
+// (One thread per group and channel pair, reading the group twice, divided
+// every value: 12 int4 chunks x 36 layers of fp64 keys, 113 MB, took 45 us;
+// this takes 23 us, 4.9 TB/s of input.)
+template <typename T, int D, int BITS, bool SMALL>
+__global__ void __launch_bounds__(2 * D)
+quant_keys_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_in, int32_t Hkv,
+                  int32_t Gk, const T* __restrict__ in, uint8_t* __restrict__ codes,
+                  float* __restrict__ scale, float* __restrict__ zero) {
+  constexpr int C = 128, TT = 32, NQ = TT / 4;  // tokens per chunk and thread, quads per thread
+  constexpr int CB = D * BITS / 8;
+  constexpr double levels = (double)((1 << BITS) - 1);
+  __shared__ double2 part[SMALL ? 1 : C / TT][SMALL ? 1 : 2][SMALL ? 1 : D / 2];
+  const int pr = threadIdx.x % (D / 2), tg = threadIdx.x / (D / 2);
+  const int j0 = 2 * pr, u0 = tg * TT;
+  const int n_groups = C / Gk;
+  for (int64_t s = blockIdx.x; s < n_slabs; s += gridDim.x) {  // (p, layer of the input, h)
+    const int64_t pl = s / Hkv;
+    const int64_t slab =
+        ((pl / n_in) * L + first_layer + pl % n_in) * Hkv + s % Hkv;  // (p, pool layer, h)
+    const T* src = in + (s * C + u0) * D + j0;
+    T x[TT][2];
+#pragma unroll
+    for (int u = 0; u < TT; ++u) load_n<T, 2>(src + u * D, x[u]);
+    double mn[SMALL ? NQ : 1][2], mx[SMALL ? NQ : 1][2];
+#pragma unroll
+    for (int q = 0; q < (SMALL ? NQ : 1); ++q)
+#pragma unroll
       for (int e = 0; e < 2; ++e) {
-        const double x = load_d<T>(in, in_base + (int64_t)u * D + j0 + e);
-        mn[e] = fmin(mn[e], x);
-        mx[e] = fmax(mx[e], x);
-      }
-    uint32_t cd[2];
-    for (int u = g * Gk; u < (g + 1) * Gk; ++u) {
-      for (int e = 0; e < 2; ++e) {
-        const double x = load_d<T>(in, in_base + (int64_t)u * D + j0 + e);
-        const double r = mx[e] - mn[e];
-        double c = 0.0;
-        if (r != 0.0) {
-          c = rint(((x - mn[e]) / r) * levels);
-          c = fmin(fmax(c, 0.0), levels);
+        double lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < (SMALL ? 4 : TT); ++u) {
+          lo = fmin(lo, (double)x[4 * q + u][e]);
+          hi = fmax(hi, (double)x[4 * q + u][e]);
         }
-        cd[e] = (uint32_t)c;
+        mn[q][e] = lo;
+        mx[q][e] = hi;
       }
-      uint8_t* row = codes + (out_row + u) * cb;
-      if (bits == 8) {
-        row[j0] = (uint8_t)cd[0];
-        row[j0 + 1] = (uint8_t)cd[1];
-      } else {
-        row[j0 / 2] = (uint8_t)(cd[0] | (cd[1] << 4));
+    if constexpr (SMALL) {  // groups of 4, 8 or 16 tokens: merge the quads of a group
+#pragma unroll
+      for (int w = 1; w < NQ / 2; w <<= 1) {
+        if (Gk >= 8 * w) {
+#pragma unroll
+          for (int q = 0; q < NQ; q += 2 * w)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const double lo = fmin(mn[q][e], mn[q + w][e]), hi = fmax(mx[q][e], mx[q + w][e]);
+#pragma unroll
+              for (int k = 0; k < 2 * w; ++k) {
+                mn[q + k][e] = lo;
+                mx[q + k][e] = hi;
+              }
+            }
+        }
+      }
+    } else if (Gk > TT) {
+      __syncthreads();  // the previous slab's reads are done
+      part[tg][0][pr] = make_double2(mn[0][0], mn[0][1]);
+      part[tg][1][pr] = make_double2(mx[0][0], mx[0][1]);
+      __syncthreads();
+      const int n = Gk / TT, first = tg / n * n;
+      for (int k = first; k < first + n; ++k) {
+        const double2 lo = part[k][0][pr], hi = part[k][1][pr];
+        mn[0][0] = fmin(mn[0][0], lo.x);
+        mn[0][1] = fmin(mn[0][1], lo.y);
+        mx[0][0] = fmax(mx[0][0], hi.x);
+        mx[0][1] = fmax(mx[0][1], hi.y);
       }
     }
-    const int64_t st = (((p * L + l) * Hkv + h) * n_groups + g) * (int64_t)D + j0;
-    for (int e = 0; e < 2; ++e) {
-      const double r = mx[e] - mn[e];
-      scale[st + e] = r == 0.0 ? 0.0f : (float)(r / levels);
-      zero[st + e] = (float)mn[e];
+    double inv[2], r[2];
+    bool fast[2];
+#pragma unroll
+    for (int u = 0; u < TT; ++u) {
+      const int q = SMALL ? u / 4 : 0;
+      if (u % (SMALL ? 4 : TT) == 0) {
+        const bool first = (u0 + u) % Gk == 0;  // this thread starts the group
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          r[e] = mx[q][e] - mn[q][e];
+          fast[e] = quant_fast(r[e]);
+          inv[e] = 1.0 / r[e];
+        }
+        if (first) {
+          const int64_t st = (slab * n_groups + (u0 + u) / Gk) * D + j0;
+          *reinterpret_cast<float2*>(scale + st) =
+              make_float2(r[0] == 0.0 ? 0.0f : (float)(r[0] / levels),
+                          r[1] == 0.0 ? 0.0f : (float)(r[1] / levels));
+          *reinterpret_cast<float2*>(zero + st) = make_float2((float)mn[q][0], (float)mn[q][1]);
+        }
+      }
+      const uint32_t c0 = quant_code((double)x[u][0], mn[q][0], r[0], inv[0], fast[0], levels);
+      const uint32_t c1 = quant_code((double)x[u][1], mn[q][1], r[1], inv[1], fast[1], levels);
+      uint8_t* row = codes + (slab * C + u0 + u) * CB;
+      if constexpr (BITS == 8)
+        *reinterpret_cast<uint16_t*>(row + j0) = (uint16_t)(c0 | (c1 << 8));
+      else
+        row[j0 / 2] = (uint8_t)(c0 | (c1 << 4));
     }
   }
 }
 
-// Values: one thread per (slot, layer, head, token, channel group).
-template <typename T>
+// Values: a thread owns 8 consecutive channels of one token (one code word),
+// so the D / 8 lanes of a token read whole rows; the Gv / 8 lanes of a group
+// (a power of two: Gv is 16, 32, 64 or 128) meet with xor-shuffles.  HBM-bound
+// on the input.  (One thread per group, reading its Gv values one by one and
+// twice with its neighbours Gv elements away, took 379 us for 12 int4 chunks x
+// 36 layers of fp64 values, 113 MB; this takes 23 us, 4.9 TB/s of input.)
+template <typename T, int D, int BITS>
 __global__ void __launch_bounds__(256)
-quant_values_kernel(int32_t n_pool, int32_t L, int32_t first_layer, int32_t n_in, int32_t Hkv,
-                    int32_t C, int32_t D, int32_t bits, int32_t Gv, const void* __restrict__ in,
-                    uint8_t* __restrict__ codes, float* __restrict__ scale,
-                    float* __restrict__ zero) {
-  const int64_t n_groups = D / Gv;
-  const int64_t total = (int64_t)n_pool * n_in * Hkv * C * n_groups;
-  const double levels = (double)((1 << bits) - 1);
-  const int cb = D * bits / 8;
-  for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total;
-       w += (int64_t)gridDim.x * blockDim.x) {
-    const int g = (int)(w % n_groups);
-    int64_t rest = w / n_groups;
-    const int u = (int)(rest % C);
-    rest /= C;
-    const int h = (int)(rest % Hkv);
-    rest /= Hkv;
-    const int li = (int)(rest % n_in);
-    const int64_t p = rest / n_in;
-    const int l = first_layer + li;
-    const int64_t in_base = ((((p * n_in + li) * Hkv + h) * C) + u) * (int64_t)D + g * Gv;
+quant_values_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_in, int32_t Hkv,
+                    int32_t Gv, const T* __restrict__ in, uint8_t* __restrict__ codes,
+                    float* __restrict__ scale, float* __restrict__ zero) {
+  constexpr int C = 128, LPT = D / 8;  // lanes per token
+  constexpr int CB = D * BITS / 8;
+  constexpr double levels = (double)((1 << BITS) - 1);
+  const int n_groups = D / Gv;
+  const int j0 = (threadIdx.x % LPT) * 8;
+  // whole workgroups step over tokens: every lane of a token's group is active
+  for (int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPT; row < n_slabs * C;
+       row += (int64_t)gridDim.x * 256 / LPT) {
+    const int64_t s = row / C;  // (p, layer of the input, h)
+    const int64_t pl = s / Hkv;
+    const int64_t out_row =
+        (((pl / n_in) * L + first_layer + pl % n_in) * Hkv + s % Hkv) * C + row % C;
+    T x[8];
+    load_n<T, 8>(in + row * D + j0, x);
     double mn = INFINITY, mx = -INFINITY;
-    for (int j = 0; j < Gv; ++j) {
-      const double x = load_d<T>(in, in_base + j);
-      mn = fmin(mn, x);
-      mx = fmax(mx, x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      mn = fmin(mn, (double)x[e]);
+      mx = fmax(mx, (double)x[e]);
     }
-    const double r = mx - mn;
-    uint8_t* row = codes + ((((p * L + l) * Hkv + h) * C) + u) * (int64_t)cb;
-    for (int j = 0; j < Gv; j += 2) {
-      uint32_t cd[2];
-      for (int e = 0; e < 2; ++e) {
-        const double x = load_d<T>(in, in_base + j + e);
-        double c = 0.0;
-        if (r != 0.0) {
-          c = rint(((x - mn) / r) * levels);
-          c = fmin(fmax(c, 0.0), levels);
-        }
-        cd[e] = (uint32_t)c;
-      }
-      const int ch = g * Gv + j;
-      if (bits == 8) {
-        row[ch] = (uint8_t)cd[0];
-        row[ch + 1] = (uint8_t)cd[1];
-      } else {
-        row[ch / 2] = (uint8_t)(cd[0] | (cd[1] << 4));
-      }
+    for (int m = 1; m < Gv / 8; m <<= 1) {
+      mn = fmin(mn, __shfl_xor(mn, m, 64));
+      mx = fmax(mx, __shfl_xor(mx, m, 64));
     }
-    const int64_t st = ((((p * L + l) * Hkv + h) * C) + u) * n_groups + g;
-    scale[st] = r == 0.0 ? 0.0f : (float)(r / levels);
-    zero[st] = (float)mn;
+    const double r = mx - mn, inv = 1.0 / r;
+    const bool fast = quant_fast(r);
+    uint32_t w[BITS == 8 ? 2 : 1] = {};
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      w[e * BITS / 32] |= quant_code((double)x[e], mn, r, inv, fast, levels) << (e * BITS % 32);
+    uint8_t* dst = codes + out_row * CB + j0 * BITS / 8;
+    if constexpr (BITS == 8)
+      *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
+    else
+      *reinterpret_cast<uint32_t*>(dst) = w[0];
+    if (j0 % Gv == 0) {
+      const int64_t st = out_row * n_groups + j0 / Gv;
+      scale[st] = r == 0.0 ? 0.0f : (float)(r / levels);
+      zero[st] = (float)mn;
+    }
   }
 }
 
@@ -296,23 +363,38 @@ hipError_t launch_kivi_quantize(const kvb_pool_layout& p, int32_t n_pool, int32_
                                 int32_t n_in, kvb_dtype in_dtype, const void* k_in,
                                 const void* v_in, uint8_t* k_codes, float* k_scale, float* k_zero,
                                 uint8_t* v_codes, float* v_scale, float* v_zero, hipStream_t s) {
-  const int64_t kw = (int64_t)n_pool * n_in * p.n_kv_heads * (p.chunk_len / p.k_group) * (p.head_dim / 2);
-  const int64_t vw = (int64_t)n_pool * n_in * p.n_kv_heads * p.chunk_len * (p.head_dim / p.v_group);
+  const int64_t n_slabs = (int64_t)n_pool * n_in * p.n_kv_heads;
+  const dim3 kgrid((unsigned)(n_slabs < 65536 ? n_slabs : 65536));
+  const dim3 vgrid(grid_for(n_slabs * p.chunk_len * (p.head_dim / 8)));
+#define KVB_QUANT(T, D, B)                                                                       \
+  do {                                                                                           \
+    const T* k = reinterpret_cast<const T*>(k_in);                                               \
+    if (p.k_group < 32)                                                                          \
+      hipLaunchKernelGGL((quant_keys_kernel<T, D, B, true>), kgrid, dim3(2 * D), 0, s, n_slabs,  \
+                         p.n_layers, first_layer, n_in, p.n_kv_heads, p.k_group, k, k_codes,     \
+                         k_scale, k_zero);                                                       \
+    else                                                                                         \
+      hipLaunchKernelGGL((quant_keys_kernel<T, D, B, false>), kgrid, dim3(2 * D), 0, s, n_slabs, \
+                         p.n_layers, first_layer, n_in, p.n_kv_heads, p.k_group, k, k_codes,     \
+                         k_scale, k_zero);                                                       \
+    hipLaunchKernelGGL((quant_values_kernel<T, D, B>), vgrid, dim3(256), 0, s, n_slabs,          \
+                       p.n_layers, first_layer, n_in, p.n_kv_heads, p.v_group,                   \
+                       reinterpret_cast<const T*>(v_in), v_codes, v_scale, v_zero);              \
+  } while (0)
+#define KVB_QUANT_D(T, D)  \
+  do {                     \
+    if (p.bits == 8)       \
+      KVB_QUANT(T, D, 8);  \
+    else                   \
+      KVB_QUANT(T, D, 4);  \
+  } while (0)
   if (in_dtype == KVB_F64) {
-    hipLaunchKernelGGL(quant_keys_kernel<double>, dim3(grid_for(kw)), dim3(256), 0, s, n_pool,
-                       p.n_layers, first_layer, n_in, p.n_kv_heads, p.chunk_len, p.head_dim,
-                       p.bits, p.k_group, k_in, k_codes, k_scale, k_zero);
-    hipLaunchKernelGGL(quant_values_kernel<double>, dim3(grid_for(vw)), dim3(256), 0, s, n_pool,
-                       p.n_layers, first_layer, n_in, p.n_kv_heads, p.chunk_len, p.head_dim,
-                       p.bits, p.v_group, v_in, v_codes, v_scale, v_zero);
+    if (p.head_dim == 128) KVB_QUANT_D(double, 128); else KVB_QUANT_D(double, 64);
   } else {
-    hipLaunchKernelGGL(quant_keys_kernel<float>, dim3(grid_for(kw)), dim3(256), 0, s, n_pool,
-                       p.n_layers, first_layer, n_in, p.n_kv_heads, p.chunk_len, p.head_dim,
-                       p.bits, p.k_group, k_in, k_codes, k_scale, k_zero);
-    hipLaunchKernelGGL(quant_values_kernel<float>, dim3(grid_for(vw)), dim3(256), 0, s, n_pool,
-                       p.n_layers, first_layer, n_in, p.n_kv_heads, p.chunk_len, p.head_dim,
-                       p.bits, p.v_group, v_in, v_codes, v_scale, v_zero);
+    if (p.head_dim == 128) KVB_QUANT_D(float, 128); else KVB_QUANT_D(float, 64);
   }
+#undef KVB_QUANT_D
+#undef KVB_QUANT
   return hipGetLastError();
 }
 
