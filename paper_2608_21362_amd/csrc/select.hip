@@ -10,10 +10,20 @@
 // output is ascending without a sort and no atomic decides an order.  LDS
 // atomics only count histogram bins.
 //
-// Segments of up to 48K rows use select_reg_kernel: every thread keeps the keys
-// and flags of its KPT rows (rows lo + j * 1024 + tid) in registers, so the
-// four histogram passes touch no memory but LDS, and the compaction takes one
-// ballot per register slot with a single block-wide prefix over all of them.
+// Segments of up to 64K rows use select_reg_kernel: the prompt's rows are split
+// into 16 equal runs, one per wave, and lane i of a wave holds the keys and
+// flags of rows i, i + 64, .. of its run in registers (coalesced loads, read
+// once), so the histogram passes touch no memory but LDS and a row's rank is
+// its wave's base plus ballots on the scalar unit.  A launch has one workgroup
+// per prompt and set, so it is bound by one CU's instruction issue (about 65
+// vector instructions per slot and wave: 0.5 us per slot).  Hence three digits
+// (12, 12 and 8 bits) instead of four of 8 bits, keys and flags folded into one
+// word per row, and an end as soon as the k-th key's bin is selected whole
+// (typically after 24 bits).  Four copies of the histogram (lane % 4) keep equal
+// keys of a wave from queueing at one word.  36 sets of 8192 rows take 9 us (22
+// with four 8-bit digits, one histogram and per-slot ranks through LDS), of
+// 32772 rows 22 us (65).  Adds to a spare word instead of a branch around rows
+// that do not count, and 16 copies of an 8-bit histogram, measured the same.
 // Longer segments use select_kernel, which re-reads the keys on every pass.
 //
 // Several prompts per set: rows go to a staging area at the prompt's own row
@@ -188,111 +198,46 @@ select_kernel(int64_t t_total, const int32_t* __restrict__ cu_seqlens, int32_t n
 }
 
 
-// Radix select of the k-th largest key among the candidate keys of this
-// thread's register slots; every thread must call.  Returns tau and how many
-// candidates equal to tau are still needed.
-template <int KPT>
-__device__ __forceinline__ void radix_select_reg(const uint32_t (&key)[KPT], uint64_t candm,
-                                                 uint32_t k, uint32_t* hist, uint32_t* sh_prefix,
-                                                 uint32_t* sh_remaining, uint32_t* tau,
-                                                 uint32_t* need_eq) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t prefix = 0, remaining = k;
-  for (int digit = 3; digit >= 0; --digit) {
-    for (int i = tid; i < 256; i += kThreads) hist[i] = 0;
-    __syncthreads();
-    const uint32_t hi_mask = digit == 3 ? 0u : (0xFFFFFFFFu << (8 * (digit + 1)));
-    int run_bin = -1;
-    uint32_t run_n = 0;
-#pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      if (!((candm >> j) & 1ull)) continue;
-      if ((key[j] & hi_mask) != (prefix & hi_mask)) continue;
-      const int bin = (key[j] >> (8 * digit)) & 0xFF;
-      if (bin == run_bin) {
-        ++run_n;
-      } else {
-        if (run_n) atomicAdd(&hist[run_bin], run_n);
-        run_bin = bin;
-        run_n = 1;
-      }
-    }
-    if (run_n) atomicAdd(&hist[run_bin], run_n);
-    __syncthreads();
-    if (wave == 0) {
-      // lane i owns bins 255-4i .. 252-4i (walking from the top)
-      uint32_t hb[4], sum = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        hb[j] = hist[255 - 4 * lane - j];
-        sum += hb[j];
-      }
-      uint32_t incl = sum;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += v;
-      }
-      const uint64_t hit = __ballot(incl >= remaining);
-      const int first = __ffsll((unsigned long long)hit) - 1;
-      if (lane == first) {
-        uint32_t cum = incl - sum;
-        for (int j = 0; j < 4; ++j) {
-          if (cum + hb[j] >= remaining) {
-            *sh_prefix = prefix | ((uint32_t)(255 - 4 * lane - j) << (8 * digit));
-            *sh_remaining = remaining - cum;
-            break;
-          }
-          cum += hb[j];
-        }
-      }
-    }
-    __syncthreads();
-    prefix = *sh_prefix;
-    remaining = *sh_remaining;
-  }
-  *tau = prefix;
-  *need_eq = remaining;
+// Inclusive prefix sum over the 64 lanes of a wave, on the vector unit (DPP
+// row shifts, then the two row broadcasts), no LDS round trips.
+__device__ __forceinline__ uint32_t wave_incl(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);  // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);  // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);  // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return x;
 }
 
-// Per-slot, per-wave counts of a bit (slot-major, then thread order) into
-// wcnt; returns the block-wide total.  Every thread must call; wcnt is valid
-// until the next call.
-template <int KPT>
-__device__ __forceinline__ uint32_t slot_counts(uint64_t bits, uint32_t (*wcnt)[kWaves],
-                                                int nslots) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();  // the previous user of wcnt is done
-#pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    if (j < nslots) {
-      const uint64_t ball = __ballot((bits >> j) & 1ull);
-      if (lane == 0) wcnt[j][wave] = (uint32_t)__popcll(ball);
-    }
-  }
-  __syncthreads();
-  uint32_t tot = 0;
-  for (int j = 0; j < nslots; ++j)
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) tot += wcnt[j][w];
-  return tot;
+// Set lanes of a wave's ballot below this lane.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t ball) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(ball >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)ball, 0u));
 }
 
-// Exclusive rank of slot j's bit among all set bits (slot-major, then thread),
-// from the counts of slot_counts and the running total of slots before j.
-__device__ __forceinline__ uint32_t slot_rank(uint64_t bits, int j, const uint32_t (*wcnt)[kWaves],
-                                              uint32_t run_before, uint32_t* slot_total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t ball = __ballot((bits >> j) & 1ull);
-  uint32_t before = 0, tot = 0;
+constexpr int kBins = 4096;           // bins of a digit of up to 12 bits
+constexpr int kCopies = 4;            // copies of every histogram (lane % 4)
+constexpr int kCopyWords = kBins + 16;  // a bin's copies lie in different banks
+
+// order_key for the register kernel, where 0 stands for a row that is no
+// candidate: NaN is 1, below every number (the lowest, -inf, is 0x007FFFFF).
+__device__ __forceinline__ uint32_t order_key_from1(float f) {
+  const uint32_t u = __float_as_uint(f + 0.0f);  // -0 -> +0
+  const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+  return f != f ? 1u : key;
+}
+
+// Runs body(j) for the register slots of this thread, kBatch of them behind one
+// uniform branch; slots from nslots on hold no rows.
+template <int KPT, int kBatch, typename F>
+__device__ __forceinline__ void for_slots(int nslots, F body) {
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
-    const uint32_t c = wcnt[j][w];
-    before += (w < wave) ? c : 0u;
-    tot += c;
-  }
-  *slot_total = tot;
-  return run_before + before + (uint32_t)__popcll(ball & ((1ull << lane) - 1ull));
+  for (int j0 = 0; j0 < KPT; j0 += kBatch)
+    if (j0 < nslots) {
+#pragma unroll
+      for (int j = j0; j < j0 + kBatch; ++j) body(j);
+    }
 }
 
 template <int KPT>
@@ -302,82 +247,165 @@ select_reg_kernel(int64_t t_total, const int32_t* __restrict__ cu_seqlens, int32
                   const int32_t* __restrict__ k_per_seq, int32_t* __restrict__ rows_out,
                   int32_t* __restrict__ cu_rows, int32_t* __restrict__ staging,
                   int32_t* __restrict__ counts) {
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t wcnt[KPT][kWaves];
-  __shared__ uint32_t sh_prefix, sh_remaining;
+  __shared__ uint4 hist4[kCopies * kCopyWords / 4];
+  __shared__ uint32_t wave_tot[kWaves], eq_tot[kWaves], sel_tot[kWaves];
+  __shared__ uint32_t sh_bin, sh_in_bin, sh_left;
+  uint32_t* const hist = reinterpret_cast<uint32_t*>(hist4);
+  constexpr int kBatch = KPT < 32 ? 4 : 8;
   const int b = blockIdx.x;
   const int64_t set = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int64_t lo = cu_seqlens[b], hi = cu_seqlens[b + 1];
-  const int nslots = (int)((hi - lo + kThreads - 1) / kThreads);  // <= KPT by the launch
-  const float* dl = delta + set * t_total;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t lo = cu_seqlens[b];
+  const int n = (int)(cu_seqlens[b + 1] - lo);
+  const int32_t k = k_per_seq[set * n_seqs + b];
+  const int nslots = (n + kThreads - 1) / kThreads;  // <= KPT by the launch
+  const float* dl = delta + set * t_total + lo;
+  const uint8_t* fl = flags + lo;
+  const int first = wave * 64 * nslots + lane;  // slot j: row lo + first + 64 j
 
-  // this thread's rows lo + j * kThreads + tid: keys and flags, loaded once
-  uint32_t key[KPT];
-  uint64_t candm = 0, forcedm = 0;
+  for (int i = tid; i < (int)(sizeof(hist4) / sizeof(uint4)); i += kThreads)
+    hist4[i] = make_uint4(0, 0, 0, 0);
+
+  // this thread's keys (0: no candidate) and forced bits, loaded once.  Loads
+  // are unconditional (past the segment its last row is read again, and a row
+  // that is no candidate has a deviation in range that is never used), and all
+  // of them (half of them from 48 slots on, for the registers) go out before any is used.
+  constexpr int kStage = KPT > 32 ? KPT / 2 : KPT;
+  uint32_t key[KPT] = {}, forced[(KPT + 31) / 32] = {};
 #pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    key[j] = 0;
-    const int64_t r = lo + (int64_t)j * kThreads + tid;
-    if (j < nslots && r < hi) {
-      const uint32_t f = flags[r];
-      if (f & KVB_ROW_CANDIDATE) {
-        candm |= 1ull << j;
-        key[j] = order_key(dl[r]);
-      }
-      if (f & KVB_ROW_FORCED) forcedm |= 1ull << j;
-    }
+  for (int s0 = 0; s0 < KPT; s0 += kStage) {
+    uint32_t f[kStage];
+    for_slots<kStage, kBatch>(nslots - s0, [&](int i) {
+      const uint32_t r = (uint32_t)min(first + 64 * (s0 + i), n - 1);
+      f[i] = fl[r];
+      key[s0 + i] = __float_as_uint(dl[r]);
+    });
+    for_slots<kStage, kBatch>(nslots - s0, [&](int i) {
+      const int j = s0 + i;
+      const uint32_t fj = j < nslots && first + 64 * j < n ? f[i] : 0u;
+      key[j] = (fj & KVB_ROW_CANDIDATE) ? order_key_from1(__uint_as_float(key[j])) : 0u;
+      forced[j / 32] |= ((fj & KVB_ROW_FORCED) ? 1u : 0u) << (j % 32);
+    });
   }
-  const uint32_t n_cand = slot_counts<KPT>(candm, wcnt, nslots);
-  int64_t k = k_per_seq[set * n_seqs + b];
-  if (k < 0) k = 0;
-  const bool take_all = k >= (int64_t)n_cand;
-  const bool take_none = k == 0;
+  __syncthreads();
 
-  uint64_t gtm = 0, eqm = 0;
-  if (take_all) {
-    gtm = candm;
-  } else if (!take_none) {
-    uint32_t tau, need_eq;
-    radix_select_reg<KPT>(key, candm, (uint32_t)k, hist, &sh_prefix, &sh_remaining, &tau,
-                          &need_eq);
+  // candidates with (key & mask) >= prefix are selected, except those equal to
+  // it past the first `remaining` of n_eq
+  uint32_t prefix = 0, mask = 0, n_eq = 0;
+  uint32_t remaining = k > 0 ? (uint32_t)k : 0u;
+  if (remaining == 0) {
+    prefix = mask = 0xFFFFFFFFu;  // above every key
+  } else {
+    // digits of 12, 12 and 8 bits
+#pragma unroll 1
+    for (int shift = 20; shift > -12; shift -= 12) {
+      const int sh = shift < 0 ? 0 : shift;
+      const uint32_t digit_mask = shift < 0 ? 0xFFu : 0xFFFu;
+      const uint32_t copy = (uint32_t)(lane % kCopies) * kCopyWords;
+      for_slots<KPT, kBatch>(nslots, [&](int j) {
+        if ((key[j] & mask) == prefix && key[j] != 0)
+          atomicAdd(&hist[copy + ((key[j] >> sh) & digit_mask)], 1u);
+      });
+      __syncthreads();
+      // thread t owns bins 4095-4t .. 4092-4t (walking from the top): adds their
+      // copies and clears them for the next digit
+      uint4 q = make_uint4(0, 0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      if ((candm >> j) & 1ull) {
-        if (key[j] > tau) gtm |= 1ull << j;
-        if (key[j] == tau) eqm |= 1ull << j;
+      for (int c = 0; c < kCopies; ++c) {
+        uint4* p = hist4 + c * (kCopyWords / 4) + (kThreads - 1 - tid);
+        const uint4 x = *p;
+        *p = make_uint4(0, 0, 0, 0);
+        q.x += x.x;
+        q.y += x.y;
+        q.z += x.z;
+        q.w += x.w;
       }
-    }
-    // the first need_eq keys equal to tau, in row order (the lower row wins a tie)
-    const uint32_t n_eq = slot_counts<KPT>(eqm, wcnt, nslots);
-    if (need_eq < n_eq) {
-      uint32_t run = 0;
-      uint64_t keep = 0;
+      const uint32_t hb[4] = {q.w, q.z, q.y, q.x};
+      const uint32_t sum = q.x + q.y + q.z + q.w;
+      const uint32_t incl = wave_incl(sum);
+      if (lane == 63) wave_tot[wave] = incl;
+      __syncthreads();
+      uint32_t before = 0, total = 0;
 #pragma unroll
-      for (int j = 0; j < KPT; ++j) {
-        if (j < nslots) {
-          uint32_t tot;
-          const uint32_t rk = slot_rank(eqm, j, wcnt, run, &tot);
-          if (((eqm >> j) & 1ull) && rk < need_eq) keep |= 1ull << j;
-          run += tot;
+      for (int w = 0; w < kWaves; ++w) {
+        const uint32_t c = wave_tot[w];
+        before += w < wave ? c : 0u;
+        total += c;
+      }
+      if (shift == 20 && remaining >= total) {
+        prefix = 1;  // k reaches every candidate
+        mask = 0xFFFFFFFFu;
+        n_eq = remaining;
+        break;
+      }
+      uint32_t cum = before + incl - sum;
+      if (cum < remaining && cum + sum >= remaining) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          if (cum < remaining && cum + hb[j] >= remaining) {
+            sh_bin = (uint32_t)(kBins - 1 - 4 * tid - j);
+            sh_in_bin = hb[j];
+            sh_left = remaining - cum;
+          }
+          cum += hb[j];
         }
       }
-      eqm = keep;
+      __syncthreads();
+      prefix |= sh_bin << sh;
+      mask |= digit_mask << sh;
+      n_eq = sh_in_bin;
+      remaining = sh_left;
+      if (remaining == n_eq) break;  // the whole bin is selected: no finer digit matters
+    }
+    if (prefix == 0) {  // a bin of NaN keys alone: keep rows that are no candidates out
+      prefix = 1;
+      mask = 0xFFFFFFFFu;
+    }
+    if (remaining < n_eq) {
+      // of the keys equal to the k-th only the first `remaining` in row order
+      // (the lower row wins a tie): the others leave the candidates
+      uint32_t mine = 0;
+      for_slots<KPT, kBatch>(nslots, [&](int j) {
+        mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(key[j] == prefix));
+      });
+      if (lane == 0) eq_tot[wave] = mine;
+      __syncthreads();
+      uint32_t run = 0;
+      for (int w = 0; w < wave; ++w) run += eq_tot[w];
+      for_slots<KPT, kBatch>(nslots, [&](int j) {
+        const bool eq = key[j] == prefix;
+        const uint64_t ball = __builtin_amdgcn_ballot_w64(eq);
+        if (eq && run + lanes_below(ball) >= remaining) key[j] = 0;
+        run += (uint32_t)__popcll(ball);
+      });
     }
   }
-  const uint64_t selm = forcedm | gtm | eqm;
-  const uint32_t n_sel = slot_counts<KPT>(selm, wcnt, nslots);
-  int32_t* dst = (n_seqs == 1) ? rows_out + set * t_total : staging + set * t_total + lo;
-  uint32_t run = 0;
+
+  // ascending rows: waves in order, slots in order, lanes in order
+  const auto selected = [&](int j) {
+    return (key[j] & mask) >= prefix || ((forced[j / 32] >> (j % 32)) & 1u);
+  };
+  uint32_t mine = 0;
+  for_slots<KPT, kBatch>(nslots, [&](int j) {
+    mine += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(selected(j)));
+  });
+  if (lane == 0) sel_tot[wave] = mine;
+  __syncthreads();
+  uint32_t run = 0, n_sel = 0;
 #pragma unroll
-  for (int j = 0; j < KPT; ++j) {
-    if (j < nslots) {
-      uint32_t tot;
-      const uint32_t rk = slot_rank(selm, j, wcnt, run, &tot);
-      if ((selm >> j) & 1ull) dst[rk] = (int32_t)(lo + (int64_t)j * kThreads + tid);
-      run += tot;
-    }
+  for (int w = 0; w < kWaves; ++w) {
+    const uint32_t c = sel_tot[w];
+    run += w < wave ? c : 0u;
+    n_sel += c;
   }
+  int32_t* dst = (n_seqs == 1) ? rows_out + set * t_total : staging + set * t_total + lo;
+  for_slots<KPT, kBatch>(nslots, [&](int j) {
+    const bool sel = selected(j);
+    const uint64_t ball = __builtin_amdgcn_ballot_w64(sel);
+    if (sel) dst[run + lanes_below(ball)] = (int32_t)lo + first + 64 * j;
+    run += (uint32_t)__popcll(ball);
+  });
   if (tid == 0) {
     if (n_seqs == 1) {
       cu_rows[set * 2] = 0;
@@ -433,7 +461,8 @@ hipError_t launch_select(int32_t n_sets, int64_t t_total, const int32_t* cu_seql
     const size_t st = (size_t)n_sets * (size_t)t_total * sizeof(int32_t);
     counts = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + ((st + 255) / 256) * 256);
   }
-  // the longest prompt is at most t_total rows: pick the register-slot count from it
+  // the longest prompt is at most t_total rows: pick the register-slot count
+  // from it (64 slots: the slot bits of a thread are one 64-bit word)
   const dim3 grid(n_seqs, n_sets);
 #define KVB_SELECT_REG(K)                                                                       \
   hipLaunchKernelGGL(select_reg_kernel<K>, grid, dim3(kThreads), 0, s, t_total, cu_seqlens,     \
@@ -446,6 +475,8 @@ hipError_t launch_select(int32_t n_sets, int64_t t_total, const int32_t* cu_seql
     KVB_SELECT_REG(32);
   else if (t_total <= 48 * kThreads)
     KVB_SELECT_REG(48);
+  else if (t_total <= 64 * kThreads)
+    KVB_SELECT_REG(64);
   else
     hipLaunchKernelGGL(select_kernel, grid, dim3(kThreads), 0, s, t_total, cu_seqlens, n_seqs,
                        delta, row_flags, k_per_seq, rows, cu_rows, staging, counts);
