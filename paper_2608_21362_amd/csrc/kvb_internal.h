@@ -65,6 +65,7 @@ struct AttnPlan {
   int rows_per_tile;   // selected rows per workgroup tile
   int tile_slots;      // tile slots per (layer, kv head)
   int n_tiles;         // layers x kv heads x tile slots
+  int split_slots;     // slots of 32-query tiles per (layer, kv head)
   int n_wg_max;        // most attention workgroups a launch uses
   int n_rec;           // partial records (two per workgroup)
   int max_seq_len;     // longest prompt (bounds the key blocks of any tile)

@@ -10,7 +10,8 @@
 //                    takes as its operand (exact for |v| < 65536: a bf16
 //                    significand fits an fp16 one; values fp16 cannot hold are
 //                    reported in a status word)
-//   attn_kernel      the attention itself (below)
+//   attn_kernel      the attention itself (below); launches of few short tiles
+//                    take attn_split_kernel instead
 //   combine_kernel   merges the partial records of tiles that were cut between
 //                    workgroups (balanced ranges only)
 //
@@ -182,6 +183,39 @@ __device__ __forceinline__ bool find_tile(const int32_t* cur, int n_seqs, int ro
       return true;
     }
     acc += nt;
+  }
+  return false;
+}
+
+// Tile of slot `slot`: prompts' tiles are numbered one prompt after another.
+// Every lane of a wave looks at one prompt and a prefix sum finds the slot's
+// (one thread walking the prompts is a chain of dependent loads).  Wave-uniform;
+// every lane must call.
+__device__ __forceinline__ bool find_tile_wave(const int32_t* cur, int n_seqs, int rows_per_tile,
+                                               int slot, Tile* t) {
+  const int lane = threadIdx.x & 63;
+  int acc = 0;
+  for (int b0 = 0; b0 < n_seqs; b0 += 64) {
+    const int b = min(b0 + lane, n_seqs - 1);
+    const int lo = cur[b], hi = cur[b + 1];
+    const int nt = b0 + lane < n_seqs ? (hi - lo + rows_per_tile - 1) / rows_per_tile : 0;
+    int incl = nt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += y;
+    }
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(slot < acc + incl);
+    if (hit != 0) {
+      const int at = __ffsll((unsigned long long)hit) - 1;
+      const int before = acc + __builtin_amdgcn_readlane(incl - nt, at);
+      const int first = __builtin_amdgcn_readlane(lo, at);
+      t->b = b0 + at;
+      t->r_begin = first + (slot - before) * rows_per_tile;
+      t->r_end = min(t->r_begin + rows_per_tile, __builtin_amdgcn_readlane(hi, at));
+      return true;
+    }
+    acc += __builtin_amdgcn_readlane(incl, 63);
   }
   return false;
 }
@@ -847,9 +881,9 @@ patch_kernel(int32_t L, int32_t Hkv, int32_t D, int64_t t_total, int32_t n_seqs,
   }
 }
 
-// Two launch shapes:
+// Two launch shapes (a third, for few short tiles, is attn_split_kernel):
 //  * whole tiles (many tiles): workgroup t finishes tile t;
-//  * balanced ranges (few tiles): workgroup w walks the tiles that overlap its
+//  * balanced ranges (few long tiles): workgroup w walks the tiles that overlap its
 //    units [unit_start(w), unit_start(w + 1)); a tile whose blocks it covers
 //    whole is finished here, the cut ones (at most its first and its last)
 //    leave partial records 2w and 2w + 1.
@@ -874,13 +908,13 @@ attn_kernel(int32_t balanced, int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t 
     const int lg = t % n_lg;
     const int64_t set = rows_per_layer ? lg / Hkv : 0;
     Tile tile;
-    if (!find_tile(cu_rows + set * (n_seqs + 1), n_seqs, rows_per_tile, t / n_lg, &tile))
+    if (!find_tile_wave(cu_rows + set * (n_seqs + 1), n_seqs, rows_per_tile, t / n_lg, &tile))
       return;
     SegTile tl;
     tl.lg = lg;
     tl.r_begin = tile.r_begin;
     tl.r_end = tile.r_end;
-    tl.kstart = cu_seqlens[tile.b];
+    tl.kstart = __builtin_amdgcn_readfirstlane(cu_seqlens[tile.b]);
     tl.kend = min(rows[set * t_total + tile.r_end - 1] + 1, (int)t_total);
     const int whole = (int)((t_total + kKB - 1) / kKB) + 1;
     attend_segment<D>(tl, 0, whole, -1, n_rec, k_ring, v_ring, Hq, Hkv, log2g, t_total, rows,
@@ -924,6 +958,197 @@ attn_kernel(int32_t balanced, int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t 
       p1 = prefix[t + 1];
       mt = meta[t];
     }
+  }
+}
+
+// Key-split tiles (few, short tiles): a workgroup finishes one tile of 32 query
+// vectors (32 / G rows x G heads), its four waves taking every fourth key block
+// each: wave w blocks w, w + 4, ..  A wave streams its own K and V blocks
+// through its own LDS stage (16 KiB at d = 128), so the loop has no barrier; the
+// operands of a block are read into registers a step ahead, which frees the
+// stage for the block after it.  At the end the waves' sums are brought to a
+// common maximum and added in wave order through LDS (the stages' space): no
+// partial records, no merge launch, and a chain of a quarter of the blocks.
+// The price is four times the block loads per query of a 128-query tile, so it
+// serves launches that leave the chip idle (attn_mode).  256 tokens, 163 rows:
+// 7.5 us against 11.7 for whole tiles; 1024 tokens, 777 rows: 15 us against 25
+// for balanced ranges and their merge.  Eight waves per tile measured 8.4 and
+// 20 us, two groups of queries sharing each wave pair's blocks 10 and 21 us.
+template <int D>
+__global__ void __launch_bounds__(kThreads, 2)
+attn_split_kernel(int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t log2g, int64_t t_total,
+                  const int32_t* __restrict__ cu_seqlens, int32_t n_seqs,
+                  const int32_t* __restrict__ rows, const int32_t* __restrict__ cu_rows,
+                  int32_t rows_per_layer, int32_t rows_per_tile, int32_t tile_slots,
+                  const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
+                  const uint16_t* __restrict__ v16, float c_log2, int32_t out_f32,
+                  void* __restrict__ out) {
+  using C = AttnCfg<D>;
+  constexpr int NL = C::BLK / 1024;  // wave-wide loads per block and tensor
+  __shared__ __attribute__((aligned(1024))) char stage[kWaves][2 * C::BLK];
+  __shared__ float2 ml[kWaves][kQW];
+
+  // tiles in reverse order, as the whole-tile launch: longest first
+  const int t = n_tiles - 1 - (int)blockIdx.x;
+  const int n_lg = n_tiles / tile_slots;
+  const int lg = t % n_lg;
+  const int l = lg / Hkv, g = lg % Hkv;
+  const int64_t set = rows_per_layer ? l : 0;
+  Tile tile;
+  if (!find_tile_wave(cu_rows + set * (n_seqs + 1), n_seqs, rows_per_tile, t / n_lg, &tile)) return;
+  const int G = 1 << log2g, T = (int)t_total;
+  const int lane = threadIdx.x & 63, half = lane >> 5, n = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int32_t* rws = rows + set * t_total;
+  const int kstart = __builtin_amdgcn_readfirstlane(cu_seqlens[tile.b]);
+  const int64_t kv_base = ((int64_t)l * Hkv + g) * t_total * D;
+  const uint16_t* const kbase = kc + kv_base;
+  const uint16_t* const vbase = v16 + kv_base;
+
+  // lane offsets of the wave's loads (pieces of a block, swizzled as AttnCfg)
+  int ko[NL], vo[NL];
+#pragma unroll
+  for (int i = 0; i < NL; ++i) {
+    const int r = i * C::RPI + lane / C::CPR, slot = lane % C::CPR;
+    ko[i] = r * C::ROWB + 16 * (slot ^ C::swz_k(r));
+    vo[i] = r * C::ROWB + 16 * (slot ^ C::swz_v(r));
+  }
+  char* const k_st = stage[wave];
+  char* const v_st = stage[wave] + C::BLK;
+  const uint32_t k_lds = __builtin_amdgcn_readfirstlane(lds_addr(k_st));
+  const uint32_t v_lds = __builtin_amdgcn_readfirstlane(lds_addr(v_st));
+  // rows past the slab's end read as zero (their scores are masked)
+  auto issue = [&](const uint16_t* base, int kb, const int (&off)[NL], uint32_t lds) {
+    const i32x4 rs = buffer_rsrc(base + (int64_t)kb * D, max(T - kb, 0) * C::ROWB);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) lds_dma16(rs, lds + i * 1024, off[i], 0);
+  };
+  const int kb0 = kstart + wave * kKB;
+  constexpr int kStep = kWaves * kKB;
+
+  const int row_idx = tile.r_begin + (n >> log2g);
+  const int head = g * G + (n & (G - 1));
+  int t_q = rws[min(row_idx, tile.r_end - 1)];
+  const int t_last = rws[tile.r_end - 1], t_min = rws[tile.r_begin];
+  // the first block depends only on the prompt: it is requested with the rows
+  if (kb0 < T) {
+    issue(kbase, kb0, ko, k_lds);
+    issue(vbase, kb0, vo, v_lds);
+  }
+  const int kend = min(t_last + 1, T);
+  const bool qvalid = row_idx < tile.r_end && t_q >= kstart && t_q < kend;
+  if (!qvalid) t_q = -1;
+  bf16x8 qop[C::NS];
+  {
+    const uint16_t* qrow =
+        q + (((int64_t)l * t_total + (qvalid ? t_q : 0)) * Hq + head) * D + (D / 2) * half;
+#pragma unroll
+    for (int s = 0; s < C::NS; ++s) {
+      const uint4 w = qvalid ? *reinterpret_cast<const uint4*>(qrow + 8 * s) : make_uint4(0, 0, 0, 0);
+      qop[s] = __builtin_bit_cast(bf16x8, w);
+    }
+  }
+  const int nblk = max(kend - kstart + kKB - 1, 0) / kKB;
+  const int nb = __builtin_amdgcn_readfirstlane((nblk - wave + kWaves - 1) / kWaves);  // this wave's
+  wait_vmcnt<0>();
+  compiler_fence();
+
+  AttnState<D> st;
+#pragma unroll
+  for (int dt = 0; dt < C::ND; ++dt) st.o[dt] = f32x16{};
+  st.mc = kNoKey;
+  st.l_part = 0.0f;
+  if (nb > 0) {
+    bf16x8 kr[C::NS];
+    f16x8 vr[2][C::ND];
+    read_k<D>(k_st, lane, kr);
+    read_v<D>(v_st, lane, vr);
+    wait_lgkmcnt0();
+    compiler_fence();
+    if (nb > 1) {
+      issue(kbase, kb0 + kStep, ko, k_lds);
+      issue(vbase, kb0 + kStep, vo, v_lds);
+    }
+    f32x16 sacc = scores<D>(kr, qop);
+    // step j: probabilities of block j, scores of block j + 1, P.V of block j.
+    // In flight at its start: K then V of block j + 1.
+    for (int j = 0; j < nb; ++j) {
+      const int kb = kb0 + j * kStep;
+      const bool has1 = j + 1 < nb, has2 = j + 2 < nb;
+      if (has1) {
+        wait_vmcnt<NL>();  // K of block j + 1 landed
+        compiler_fence();
+        read_k<D>(k_st, lane, kr);
+      }
+      const bool full = kb + kKB - 1 <= t_min && kb + kKB <= kend;
+      f16x8 pb[2];
+      softmax_block<D>(sacc, st, c_log2, full, kb, t_q, kend, lane, pb);
+      if (has1) {
+        wait_lgkmcnt0();
+        compiler_fence();
+        if (has2) issue(kbase, kb + 2 * kStep, ko, k_lds);
+        sacc = scores<D>(kr, qop);
+      }
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int dt = 0; dt < C::ND; ++dt)
+          st.o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vr[ks][dt], pb[ks], st.o[dt], 0, 0, 0);
+      if (has1) {
+        if (has2)
+          wait_vmcnt<NL>();  // V of block j + 1 landed, K of block j + 2 may be in flight
+        else
+          wait_vmcnt<0>();
+        compiler_fence();
+        read_v<D>(v_st, lane, vr);
+        wait_lgkmcnt0();
+        compiler_fence();
+        if (has2) issue(vbase, kb + 2 * kStep, vo, v_lds);
+      }
+    }
+  }
+
+  // merge: the common maximum and sum of every query, then each wave adds the
+  // four waves' outputs of its quarter of the accumulator quads
+  const float l_run = sum_halves(st.l_part);
+  if (half == 0) ml[wave][n] = make_float2(st.mc, l_run);
+  __syncthreads();
+  float mc = st.mc, l_all = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) mc = fmaxf(mc, ml[w][n].x);
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) l_all += ml[w][n].y * __builtin_amdgcn_exp2f(ml[w][n].x - mc);
+  const float f = l_all > 0.0f ? __builtin_amdgcn_exp2f(st.mc - mc) / l_all : 0.0f;
+  // quad i = 4 dt + j of a lane holds channels 32 dt + 8 j + 4 half .. + 3
+  float4* const part = reinterpret_cast<float4*>(stage[wave]);
+#pragma unroll
+  for (int dt = 0; dt < C::ND; ++dt)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      part[(4 * dt + j) * 64 + lane] =
+          make_float4(st.o[dt][4 * j] * f, st.o[dt][4 * j + 1] * f, st.o[dt][4 * j + 2] * f,
+                      st.o[dt][4 * j + 3] * f);
+  __syncthreads();
+  if (!qvalid) return;
+  const int64_t ob = (((int64_t)l * t_total + t_q) * Hq + head) * D;
+#pragma unroll
+  for (int i = 0; i < 4 * C::ND / kWaves; ++i) {
+    const int quad = wave * (4 * C::ND / kWaves) + i;
+    float4 a = reinterpret_cast<const float4*>(stage[0])[quad * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      const float4 x = reinterpret_cast<const float4*>(stage[w])[quad * 64 + lane];
+      a.x += x.x;
+      a.y += x.y;
+      a.z += x.z;
+      a.w += x.w;
+    }
+    const int d0 = 8 * quad + 4 * half;
+    if (out_f32)
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + ob + d0) = a;
+    else
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(out) + ob + d0) =
+          make_uint2(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w));
   }
 }
 
@@ -1054,6 +1279,7 @@ bool attn_plan(int n_layers, int n_q_heads, int n_kv_heads, int head_dim, int64_
   plan->rows_per_tile = rows_per_tile;
   plan->tile_slots = (int)tile_slots;
   plan->n_tiles = (int)n_tiles;
+  plan->split_slots = (int)(((int64_t)max_rows * G + kQW - 1) / kQW) + n_seqs;
   plan->n_wg_max = kAttnMaxWorkgroups;
   plan->n_rec = 2 * kAttnMaxWorkgroups;
   plan->v16_in_ws = !v16_given;
@@ -1083,14 +1309,35 @@ void launch_shape(const AttnPlan& plan, int* n_wg, int* n_first) {
   *n_wg = w;
 }
 
-// One tile per workgroup (no partial records, no combine launch) when there
-// are enough tiles to keep every resident workgroup busy twice over, or when
-// no prompt is longer than kWholeTileMaxSeq rows: no tile then has more than
-// 16 key blocks, and a launch of short whole tiles ends sooner than balanced
-// ranges followed by the merge of their cut tiles.  Otherwise balanced ranges.
-constexpr int kWholeTileMaxSeq = 512;
-bool is_balanced(const AttnPlan& plan, int n_wg) {
-  return plan.n_tiles < 2 * n_wg && plan.max_seq_len > kWholeTileMaxSeq;
+// Launch shape: whole 128-query tiles, key-split 32-query tiles or balanced
+// ranges, whichever the estimate below says ends first (host arithmetic on the
+// call's sizes alone, so kvb_patch and kvb_sparse_attn_layer agree).  In
+// microseconds, fitted to 34 launches of 12 to 712 tiles over 128 to 8192 rows
+// (16 query heads, 2 kv heads, d = 128; other head shapes order the same way),
+// for which the choice is never more than 4 % slower than the best shape;
+// b = key blocks of the longest prompt, w = tiles x b per resident workgroup,
+// r = tiles per resident workgroup:
+//  * whole tiles: a block takes 0.62 us of a workgroup alone on its CU and 0.92
+//    beside a second one (17 us at 512 rows, 47 at 2048 with few tiles);
+//  * key-split: a chain of b / 4 blocks, or, with more tiles than fit, four
+//    tile starts per whole tile and its four times larger block loads (9.4 us
+//    at 512 rows, 19 at 2048 with few tiles, 39 at 2048 cold rows);
+//  * balanced ranges: the merge launch and the plan, a second segment for every
+//    cut tile, and the lowest cost per block (20 us at 512 rows, 43 at 2048 cold
+//    rows, 66 at 3072 where key-split takes 70, 58 for 15 % of 8192 rows where
+//    it takes 70).
+// With two tiles per resident workgroup whole tiles keep every CU busy and
+// need neither merge nor extra loads.
+enum class AttnMode { kWhole, kBalanced, kSplit };
+AttnMode attn_mode(const AttnPlan& plan, int n_wg) {
+  if (plan.n_tiles >= 2 * n_wg) return AttnMode::kWhole;
+  const double b = (plan.max_seq_len + kKB - 1) / kKB;
+  const double r = (double)plan.n_tiles / n_wg, w = r * b;
+  const double whole = 6.5 + b * (0.62 + 0.30 * fmin(r, 1.0)) * fmax(r, 1.0);
+  const double split = fmax(6.0 + 0.78 * ceil(b / kWaves), 2.3 + 21.0 * r + 0.79 * w);
+  const double balanced = 15.0 + 0.042 * b + 29.5 * r + 0.37 * w;
+  if (split <= whole && split <= balanced) return AttnMode::kSplit;
+  return whole <= balanced ? AttnMode::kWhole : AttnMode::kBalanced;
 }
 
 // Patch launch: copies the selected rows of n_layers layers; with plans != NULL
@@ -1123,7 +1370,7 @@ void launch_v16(int n_layers, int n_kv_heads, int head_dim, int64_t t_total, con
 
 // Attention (and, for balanced ranges, the merge of cut tiles) over an already
 // patched cache; wplan is the plan of exactly these layers.
-void launch_attend(const AttnPlan& plan, int n_wg, bool balanced, int n_q_heads, int n_kv_heads,
+void launch_attend(const AttnPlan& plan, int n_wg, AttnMode mode, int n_q_heads, int n_kv_heads,
                    int head_dim, int64_t t_total, const int32_t* cu_seqlens, int n_seqs,
                    const int32_t* rows, const int32_t* cu_rows, int rows_per_layer,
                    const uint16_t* q, const uint16_t* k_cache, const uint16_t* v16,
@@ -1132,12 +1379,27 @@ void launch_attend(const AttnPlan& plan, int n_wg, bool balanced, int n_q_heads,
   const int log2g = ilog2(n_q_heads / n_kv_heads);
   const float c_log2 = softmax_scale * 1.4426950408889634f;
   const int out_f32 = out_dtype == KVB_F32;
+  const bool balanced = mode == AttnMode::kBalanced;
   const dim3 grid(balanced ? n_wg : plan.n_tiles);
 #define KVB_ATTN(D)                                                                              \
   hipLaunchKernelGGL(attn_kernel<D>, grid, dim3(kThreads), 0, s, (int)balanced, plan.n_tiles,     \
                      n_q_heads, n_kv_heads, log2g, t_total, cu_seqlens, n_seqs, rows, cu_rows,    \
                      rows_per_layer, plan.rows_per_tile, plan.tile_slots, wplan, plan.n_wg_max,   \
                      plan.n_rec, q, k_cache, v16, c_log2, out_f32, out, parts)
+#define KVB_SPLIT(D)                                                                             \
+  hipLaunchKernelGGL(attn_split_kernel<D>, dim3(n_split), dim3(kThreads), 0, s, n_split,          \
+                     n_q_heads, n_kv_heads, log2g, t_total, cu_seqlens, n_seqs, rows, cu_rows,    \
+                     rows_per_layer, kQW >> log2g, plan.split_slots, q, k_cache, v16, c_log2,     \
+                     out_f32, out)
+  if (mode == AttnMode::kSplit) {
+    const int n_split = plan.n_tiles / plan.tile_slots * plan.split_slots;
+    if (head_dim == 128)
+      KVB_SPLIT(128);
+    else
+      KVB_SPLIT(64);
+    return;
+  }
+#undef KVB_SPLIT
 #define KVB_COMBINE(D)                                                                           \
   hipLaunchKernelGGL(combine_kernel<D>, dim3(plan.n_tiles, kQT * (D / 8) / 256), dim3(256), 0, s, \
                      plan.n_tiles, plan.n_wg_max, n_q_heads, n_kv_heads, log2g, t_total, rows,    \
@@ -1169,12 +1431,12 @@ hipError_t launch_sparse_attn(const AttnPlan& plan, int n_layers, int n_q_heads,
   float* parts = reinterpret_cast<float*>(wsb + plan.parts_offset);
   int n_wg = 0, n_first = 0;
   launch_shape(plan, &n_wg, &n_first);
-  const bool balanced = is_balanced(plan, n_wg);
+  const AttnMode mode = attn_mode(plan, n_wg);
   launch_patch(n_layers, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs, rows, cu_rows,
                rows_per_layer, max_rows, k_fresh, v_fresh, k_cache, v_cache, plan, n_wg, n_first,
-               balanced ? wplan : nullptr, 1, 0, s);
+               mode == AttnMode::kBalanced ? wplan : nullptr, 1, 0, s);
   launch_v16(n_layers, n_kv_heads, head_dim, t_total, v_cache, v16, v_status, s);
-  launch_attend(plan, n_wg, balanced, n_q_heads, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs,
+  launch_attend(plan, n_wg, mode, n_q_heads, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs,
                 rows, cu_rows, rows_per_layer, q, k_cache, v16, softmax_scale, out_dtype, out,
                 wplan, parts, s);
   return hipGetLastError();
@@ -1201,7 +1463,7 @@ hipError_t launch_patch_layers(const AttnPlan& layer_plan, int n_layers, int n_k
   int n_wg = 0, n_first = 0;
   launch_shape(layer_plan, &n_wg, &n_first);
   // plans are needed (and built) only for balanced ranges
-  int32_t* p = (plans && is_balanced(layer_plan, n_wg)) ? reinterpret_cast<int32_t*>(plans) : nullptr;
+  int32_t* p = (plans && attn_mode(layer_plan, n_wg) == AttnMode::kBalanced) ? reinterpret_cast<int32_t*>(plans) : nullptr;
   if (max_rows > 0 || p != nullptr)
     launch_patch(n_layers, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs, rows, cu_rows,
                  rows_per_layer, max_rows, k_fresh, v_fresh, k_cache, v_cache, layer_plan, n_wg,
@@ -1221,7 +1483,7 @@ hipError_t launch_sparse_attn_layer(const AttnPlan& layer_plan, int layer, int n
                                     void* out, void* workspace, hipStream_t s) {
   int n_wg = 0, n_first = 0;
   launch_shape(layer_plan, &n_wg, &n_first);
-  const bool balanced = is_balanced(layer_plan, n_wg);
+  const AttnMode mode = attn_mode(layer_plan, n_wg);
   const int64_t set = rows_per_layer ? layer : 0;
   const int64_t kv = (int64_t)layer * n_kv_heads * t_total * head_dim;
   const int64_t qo = (int64_t)layer * t_total * n_q_heads * head_dim;
@@ -1230,10 +1492,10 @@ hipError_t launch_sparse_attn_layer(const AttnPlan& layer_plan, int layer, int n
   float* parts = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + layer_plan.parts_offset);
   void* out_l = out_dtype == KVB_F32 ? (void*)(reinterpret_cast<float*>(out) + qo)
                                      : (void*)(reinterpret_cast<uint16_t*>(out) + qo);
-  launch_attend(layer_plan, n_wg, balanced, n_q_heads, n_kv_heads, head_dim, t_total, cu_seqlens,
+  launch_attend(layer_plan, n_wg, mode, n_q_heads, n_kv_heads, head_dim, t_total, cu_seqlens,
                 n_seqs, rows + set * t_total, cu_rows + set * (n_seqs + 1), 0, q + qo,
                 k_cache + kv, v_cache_f16 + kv, softmax_scale, out_dtype, out_l,
-                balanced ? wplan : nullptr, parts, s);
+                mode == AttnMode::kBalanced ? wplan : nullptr, parts, s);
   return hipGetLastError();
 }
 
