@@ -971,35 +971,52 @@ attn_kernel(int32_t balanced, int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t 
 // partial records, no merge launch, and a chain of a quarter of the blocks.
 // The price is four times the block loads per query of a 128-query tile, so it
 // serves launches that leave the chip idle (attn_mode).  256 tokens, 163 rows:
-// 7.5 us against 11.7 for whole tiles; 1024 tokens, 777 rows: 15 us against 25
+// 7.0 us against 11.7 for whole tiles; 1024 tokens, 777 rows: 15 us against 25
 // for balanced ranges and their merge.  Eight waves per tile measured 8.4 and
 // 20 us, two groups of queries sharing each wave pair's blocks 10 and 21 us.
 template <int D>
 __global__ void __launch_bounds__(kThreads, 2)
-attn_split_kernel(int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t log2g, int64_t t_total,
+attn_split_kernel(int32_t Hq, int32_t Hkv, int32_t log2g, int64_t t_total,
                   const int32_t* __restrict__ cu_seqlens, int32_t n_seqs,
                   const int32_t* __restrict__ rows, const int32_t* __restrict__ cu_rows,
-                  int32_t rows_per_layer, int32_t rows_per_tile, int32_t tile_slots,
+                  int32_t rows_per_layer, int32_t rows_per_tile,
                   const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc,
                   const uint16_t* __restrict__ v16, float c_log2, int32_t out_f32,
                   void* __restrict__ out) {
   using C = AttnCfg<D>;
   constexpr int NL = C::BLK / 1024;  // wave-wide loads per block and tensor
+  static_assert(kWaves == 4, "the merge deals the output to four waves");
   __shared__ __attribute__((aligned(1024))) char stage[kWaves][2 * C::BLK];
   __shared__ float2 ml[kWaves][kQW];
 
-  // tiles in reverse order, as the whole-tile launch: longest first
-  const int t = n_tiles - 1 - (int)blockIdx.x;
-  const int n_lg = n_tiles / tile_slots;
-  const int lg = t % n_lg;
-  const int l = lg / Hkv, g = lg % Hkv;
+  // grid: (layer, kv head) x slots, the last slots first (as in the whole-tile
+  // launch: longest first)
+  const int lg = blockIdx.x, slot = (int)(gridDim.y - 1 - blockIdx.y);
+  const int l = (int)gridDim.x == Hkv ? 0 : lg / Hkv, g = lg - l * Hkv;
   const int64_t set = rows_per_layer ? l : 0;
-  Tile tile;
-  if (!find_tile_wave(cu_rows + set * (n_seqs + 1), n_seqs, rows_per_tile, t / n_lg, &tile)) return;
   const int G = 1 << log2g, T = (int)t_total;
   const int lane = threadIdx.x & 63, half = lane >> 5, n = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int32_t* rws = rows + set * t_total;
+  const int32_t* cur = cu_rows + set * (n_seqs + 1);
+
+  // the tile and this lane's query row.  One prompt: its rows are requested at
+  // once, for a list that starts at entry 0, beside the list's bounds.
+  Tile tile;
+  int t_q;
+  const int i_row = n >> log2g;
+  if (n_seqs == 1) {
+    t_q = rws[min(slot * rows_per_tile + i_row, T - 1)];
+    const int lo = cur[0], hi = cur[1];
+    tile.b = 0;
+    tile.r_begin = lo + slot * rows_per_tile;
+    tile.r_end = min(tile.r_begin + rows_per_tile, hi);
+    if (tile.r_begin >= tile.r_end) return;
+    if (lo != 0) t_q = rws[min(tile.r_begin + i_row, tile.r_end - 1)];
+  } else {
+    if (!find_tile_wave(cur, n_seqs, rows_per_tile, slot, &tile)) return;
+    t_q = rws[min(tile.r_begin + i_row, tile.r_end - 1)];
+  }
   const int kstart = __builtin_amdgcn_readfirstlane(cu_seqlens[tile.b]);
   const int64_t kv_base = ((int64_t)l * Hkv + g) * t_total * D;
   const uint16_t* const kbase = kc + kv_base;
@@ -1009,32 +1026,31 @@ attn_split_kernel(int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t log2g, int64
   int ko[NL], vo[NL];
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    const int r = i * C::RPI + lane / C::CPR, slot = lane % C::CPR;
-    ko[i] = r * C::ROWB + 16 * (slot ^ C::swz_k(r));
-    vo[i] = r * C::ROWB + 16 * (slot ^ C::swz_v(r));
+    const int r = i * C::RPI + lane / C::CPR, slot16 = lane % C::CPR;
+    ko[i] = r * C::ROWB + 16 * (slot16 ^ C::swz_k(r));
+    vo[i] = r * C::ROWB + 16 * (slot16 ^ C::swz_v(r));
   }
-  char* const k_st = stage[wave];
-  char* const v_st = stage[wave] + C::BLK;
-  const uint32_t k_lds = __builtin_amdgcn_readfirstlane(lds_addr(k_st));
-  const uint32_t v_lds = __builtin_amdgcn_readfirstlane(lds_addr(v_st));
+  // the stage: a K block, then a V block
+  char* const st0 = stage[wave];
+  const uint32_t st0_lds = __builtin_amdgcn_readfirstlane(lds_addr(st0));
   // rows past the slab's end read as zero (their scores are masked)
-  auto issue = [&](const uint16_t* base, int kb, const int (&off)[NL], uint32_t lds) {
+  auto issue = [&](const uint16_t* base, int kb, const int (&off)[NL], uint32_t at) {
     const i32x4 rs = buffer_rsrc(base + (int64_t)kb * D, max(T - kb, 0) * C::ROWB);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) lds_dma16(rs, lds + i * 1024, off[i], 0);
+    for (int i = 0; i < NL; ++i) lds_dma16(rs, st0_lds + at + i * 1024, off[i], 0);
   };
   const int kb0 = kstart + wave * kKB;
   constexpr int kStep = kWaves * kKB;
-
-  const int row_idx = tile.r_begin + (n >> log2g);
-  const int head = g * G + (n & (G - 1));
-  int t_q = rws[min(row_idx, tile.r_end - 1)];
-  const int t_last = rws[tile.r_end - 1], t_min = rws[tile.r_begin];
   // the first block depends only on the prompt: it is requested with the rows
   if (kb0 < T) {
-    issue(kbase, kb0, ko, k_lds);
-    issue(vbase, kb0, vo, v_lds);
+    issue(kbase, kb0, ko, 0);
+    issue(vbase, kb0, vo, C::BLK);
   }
+  const int n_rows = tile.r_end - tile.r_begin;
+  const int t_last = __builtin_amdgcn_readlane(t_q, (n_rows - 1) << log2g);
+  const int t_min = __builtin_amdgcn_readfirstlane(t_q);
+  const int row_idx = tile.r_begin + i_row;
+  const int head = g * G + (n & (G - 1));
   const int kend = min(t_last + 1, T);
   const bool qvalid = row_idx < tile.r_end && t_q >= kstart && t_q < kend;
   if (!qvalid) t_q = -1;
@@ -1061,24 +1077,26 @@ attn_split_kernel(int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t log2g, int64
   if (nb > 0) {
     bf16x8 kr[C::NS];
     f16x8 vr[2][C::ND];
-    read_k<D>(k_st, lane, kr);
-    read_v<D>(v_st, lane, vr);
+    read_k<D>(st0, lane, kr);
+    read_v<D>(st0 + C::BLK, lane, vr);
     wait_lgkmcnt0();
     compiler_fence();
     if (nb > 1) {
-      issue(kbase, kb0 + kStep, ko, k_lds);
-      issue(vbase, kb0 + kStep, vo, v_lds);
+      issue(kbase, kb0 + kStep, ko, 0);
+      issue(vbase, kb0 + kStep, vo, C::BLK);
     }
     f32x16 sacc = scores<D>(kr, qop);
     // step j: probabilities of block j, scores of block j + 1, P.V of block j.
-    // In flight at its start: K then V of block j + 1.
+    // In flight at its start: K then V of block j + 1.  (Two stages a wave, block
+    // j + 2 requested at the step's start, were 5 to 20 % slower: the requests
+    // then stand before the softmax instead of beside the products.)
     for (int j = 0; j < nb; ++j) {
       const int kb = kb0 + j * kStep;
       const bool has1 = j + 1 < nb, has2 = j + 2 < nb;
       if (has1) {
         wait_vmcnt<NL>();  // K of block j + 1 landed
         compiler_fence();
-        read_k<D>(k_st, lane, kr);
+        read_k<D>(st0, lane, kr);
       }
       const bool full = kb + kKB - 1 <= t_min && kb + kKB <= kend;
       f16x8 pb[2];
@@ -1086,7 +1104,7 @@ attn_split_kernel(int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t log2g, int64
       if (has1) {
         wait_lgkmcnt0();
         compiler_fence();
-        if (has2) issue(kbase, kb + 2 * kStep, ko, k_lds);
+        if (has2) issue(kbase, kb + 2 * kStep, ko, 0);
         sacc = scores<D>(kr, qop);
       }
 #pragma unroll
@@ -1100,10 +1118,10 @@ attn_split_kernel(int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t log2g, int64
         else
           wait_vmcnt<0>();
         compiler_fence();
-        read_v<D>(v_st, lane, vr);
+        read_v<D>(st0 + C::BLK, lane, vr);
         wait_lgkmcnt0();
         compiler_fence();
-        if (has2) issue(vbase, kb + 2 * kStep, vo, v_lds);
+        if (has2) issue(vbase, kb + 2 * kStep, vo, C::BLK);
       }
     }
   }
@@ -1320,8 +1338,8 @@ void launch_shape(const AttnPlan& plan, int* n_wg, int* n_first) {
 //  * whole tiles: a block takes 0.62 us of a workgroup alone on its CU and 0.92
 //    beside a second one (17 us at 512 rows, 47 at 2048 with few tiles);
 //  * key-split: a chain of b / 4 blocks, or, with more tiles than fit, four
-//    tile starts per whole tile and its four times larger block loads (9.4 us
-//    at 512 rows, 19 at 2048 with few tiles, 39 at 2048 cold rows);
+//    tile starts per whole tile and its four times larger block loads (9.0 us
+//    at 512 rows, 18 at 2048 with few tiles, 38 at 2048 cold rows);
 //  * balanced ranges: the merge launch and the plan, a second segment for every
 //    cut tile, and the lowest cost per block (20 us at 512 rows, 43 at 2048 cold
 //    rows, 66 at 3072 where key-split takes 70, 58 for 15 % of 8192 rows where
@@ -1334,7 +1352,7 @@ AttnMode attn_mode(const AttnPlan& plan, int n_wg) {
   const double b = (plan.max_seq_len + kKB - 1) / kKB;
   const double r = (double)plan.n_tiles / n_wg, w = r * b;
   const double whole = 6.5 + b * (0.62 + 0.30 * fmin(r, 1.0)) * fmax(r, 1.0);
-  const double split = fmax(6.0 + 0.78 * ceil(b / kWaves), 2.3 + 21.0 * r + 0.79 * w);
+  const double split = fmax(5.3 + 0.78 * ceil(b / kWaves), 2.3 + 21.0 * r + 0.79 * w);
   const double balanced = 15.0 + 0.042 * b + 29.5 * r + 0.37 * w;
   if (split <= whole && split <= balanced) return AttnMode::kSplit;
   return whole <= balanced ? AttnMode::kWhole : AttnMode::kBalanced;
@@ -1387,12 +1405,11 @@ void launch_attend(const AttnPlan& plan, int n_wg, AttnMode mode, int n_q_heads,
                      rows_per_layer, plan.rows_per_tile, plan.tile_slots, wplan, plan.n_wg_max,   \
                      plan.n_rec, q, k_cache, v16, c_log2, out_f32, out, parts)
 #define KVB_SPLIT(D)                                                                             \
-  hipLaunchKernelGGL(attn_split_kernel<D>, dim3(n_split), dim3(kThreads), 0, s, n_split,          \
-                     n_q_heads, n_kv_heads, log2g, t_total, cu_seqlens, n_seqs, rows, cu_rows,    \
-                     rows_per_layer, kQW >> log2g, plan.split_slots, q, k_cache, v16, c_log2,     \
-                     out_f32, out)
+  hipLaunchKernelGGL((attn_split_kernel<D>), dim3(n_lg, plan.split_slots), dim3(kThreads),   \
+                     0, s, n_q_heads, n_kv_heads, log2g, t_total, cu_seqlens, n_seqs, rows,       \
+                     cu_rows, rows_per_layer, kQW >> log2g, q, k_cache, v16, c_log2, out_f32, out)
   if (mode == AttnMode::kSplit) {
-    const int n_split = plan.n_tiles / plan.tile_slots * plan.split_slots;
+    const int n_lg = plan.n_tiles / plan.tile_slots;
     if (head_dim == 128)
       KVB_SPLIT(128);
     else
