@@ -2,12 +2,14 @@
 // position to the new one (Sec. 4.3 assembly, Sec. 3.2 R^Delta, Sec. 4.5).
 //
 // One workgroup per (chunk, layer, kv head): 128 tokens x d channels of K and
-// of V.  HBM-bound: per workgroup it reads the K and V code blocks (C*d*b/8
-// bytes each) and their float statistics, and writes 2*C*d output elements.
+// of V (small launches split the tokens, below).  HBM-bound: per workgroup it
+// reads the K and V code blocks (C*d*b/8 bytes each) and their float
+// statistics, and writes 2*C*d output elements.
 //
 // Key jobs: one thread takes 4 consecutive tokens (one statistic group,
-// Gk % 4 == 0) and 8 channel pairs (j, j + d/2); statistics and the chunk's
-// rotation row are loaded once per job and widened to double at each use.
+// Gk % 4 == 0), or one in small launches, and 8 channel pairs (j, j + d/2);
+// statistics and the chunk's rotation row are loaded once per job and widened
+// to double at each use.
 // Value pieces: one thread takes one token and 8 consecutive channels (one statistic group,
 // Gv % 8 == 0; the API asks Gv % 16), so 16 (d = 128) or 8 (d = 64) lanes
 // store a whole row and a wave's stores are contiguous.  Every value input of
@@ -27,9 +29,9 @@
 // every key job also reads the fresh key pieces of its tokens and accumulates
 // dot and both squared norms in double over the bf16 values it stores (Alg. 2
 // step 2 on the stitched rows, K only, per layer).  The eight (d = 128) or four
-// (d = 64) lanes of a token quad combine their sums with xor-shuffles, every
+// (d = 64) lanes of a job combine their sums with xor-shuffles, every
 // lane forms the head's cosine and adds it to the token's running sum, and after
-// the last head one lane per quad writes delta for its four tokens.  Summing
+// the last head one lane per job writes delta for its tokens.  Summing
 // dot and both norms in one order keeps identical rows at delta = 0 exactly.
 #include <math.h>
 
@@ -41,7 +43,7 @@ namespace {
 
 constexpr int kC = 128;
 
-// sum of x over the TPT adjacent lanes of a token quad (TPT a power of two)
+// sum of x over the TPT adjacent lanes of a job (TPT a power of two)
 template <int TPT>
 __device__ __forceinline__ double quad_lanes_sum(double x) {
 #pragma unroll
@@ -49,7 +51,7 @@ __device__ __forceinline__ double quad_lanes_sum(double x) {
   return x;
 }
 
-template <int BITS, int D, bool BF16, bool DEV>
+template <int BITS, int D, bool BF16, bool DEV, int TOK>
 __global__ void __launch_bounds__(256)
 stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
               const uint8_t* __restrict__ k_codes, const float* __restrict__ k_scale,
@@ -61,8 +63,9 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
               float* __restrict__ delta) {
   constexpr int H = D / 2;
   constexpr int CB = D * BITS / 8;       // code bytes per token row
-  constexpr int TPT = H / 8;             // key threads per token quad
-  constexpr int KJOBS = (kC / 4) * TPT;  // 256 (d=128) or 128 (d=64)
+  constexpr int TPT = H / 8;             // key threads per token
+  constexpr int WT = TOK == 4 ? kC : 256 / TPT;  // tokens of a workgroup
+  constexpr int KJOBS = (WT / TOK) * TPT;  // 256, or 128 (d = 64, four tokens a thread)
   static_assert(!DEV || BF16, "the fused deviation reads the bf16 cache values");
   static_assert(KJOBS <= 256, "one key job per thread");
   const int c = blockIdx.x;
@@ -71,11 +74,14 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
       (int64_t)ch.dst_row + kC > t_total)
     return;
   const int ngk = kC / Gk, ngv = D / Gv;
-  // fused deviation: running cosine sum over heads of this thread's four tokens
-  double cos_sum[4] = {0.0, 0.0, 0.0, 0.0};
-  // fused: the head's key statistics (scale, then zero; at most C/4 groups)
-  // and the chunk's rotation row (cos, then sin) staged in LDS, read per token
-  __shared__ float4 st_k4[DEV ? 2 * (kC / 4) * D / 4 : 1];
+  const int u_base = (int)blockIdx.z * WT;
+  // fused deviation: running cosine sum over heads of this thread's tokens
+  double cos_sum[TOK] = {};
+  // fused: the head's key statistics of the workgroup's groups (scale, then
+  // zero; at most WT/4 groups) and the chunk's rotation row (cos, then sin)
+  // staged in LDS, read per token
+  const int g_base = u_base / Gk, n_gs = Gk < WT ? WT / Gk : 1;
+  __shared__ float4 st_k4[DEV ? 2 * (WT / 4) * D / 4 : 1];
   __shared__ float4 st_r4[DEV ? D / 4 : 1];
   const int n_heads = DEV ? Hkv : 1;
   for (int hh = 0; hh < n_heads; ++hh) {
@@ -86,9 +92,9 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
     if constexpr (DEV) {
       // the previous head's key jobs are done with the staged statistics
       __syncthreads();
-      const int n4 = ngk * D / 4;
-      const float4* ks4 = reinterpret_cast<const float4*>(k_scale + slab * ngk * D);
-      const float4* kz4 = reinterpret_cast<const float4*>(k_zero + slab * ngk * D);
+      const int n4 = n_gs * D / 4;
+      const float4* ks4 = reinterpret_cast<const float4*>(k_scale + (slab * ngk + g_base) * D);
+      const float4* kz4 = reinterpret_cast<const float4*>(k_zero + (slab * ngk + g_base) * D);
       for (int i = threadIdx.x; i < n4; i += blockDim.x) {
         st_k4[i] = ks4[i];
         st_k4[n4 + i] = kz4[i];
@@ -106,14 +112,14 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
     // while the keys are computed), the fused one after it (fewer live
     // registers during the key jobs)
     constexpr int VP = D / 8;              // pieces per token row
-    constexpr int VPT = kC * VP / 256;     // pieces per thread
+    constexpr int VPT = WT * VP / 256;     // pieces per thread
     uint32_t vw[VPT][2];
     float vsc[VPT], vzr[VPT];
     auto load_values = [&]() {
 #pragma unroll
       for (int k = 0; k < VPT; ++k) {
         const int vj = threadIdx.x + 256 * k;
-        const int u = vj / VP, j0 = (vj % VP) * 8;
+        const int u = u_base + vj / VP, j0 = (vj % VP) * 8;
         const int64_t srow = slab * kC + u;
         vsc[k] = v_scale[srow * ngv + j0 / Gv];
         vzr[k] = v_zero[srow * ngv + j0 / Gv];
@@ -128,13 +134,13 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
         }
       }
     };
-    if constexpr (!DEV) load_values();
+    if constexpr (!DEV || TOK == 1) load_values();
 
     for (int job = threadIdx.x; job < KJOBS; job += blockDim.x) {
       {
-        // ---- keys: tokens 4q..4q+3, channel pairs [8cg, 8cg + 8)
+        // ---- keys: TOK tokens from u0, channel pairs [8cg, 8cg + 8)
         const int q = job / TPT, cg = job % TPT;
-        const int u0 = 4 * q, j0 = 8 * cg;
+        const int u0 = u_base + TOK * q, j0 = 8 * cg;
         const int g = u0 / Gk;
         // statistics and rotation row of the job's channels, kept as float
         // (half the registers of double) and widened exactly at use: loaded
@@ -142,9 +148,9 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
         // the fused kernel (so they are not live while its loads are in flight)
         float s_lo[8], s_hi[8], z_lo[8], z_hi[8], cs[8], sn[8];
         auto load_stats = [&]() {
-          const float* sc = DEV ? reinterpret_cast<const float*>(st_k4) + g * D
+          const float* sc = DEV ? reinterpret_cast<const float*>(st_k4) + (g - g_base) * D
                                 : k_scale + (slab * ngk + g) * D;
-          const float* zr = DEV ? reinterpret_cast<const float*>(st_k4) + (ngk + g) * D
+          const float* zr = DEV ? reinterpret_cast<const float*>(st_k4) + (n_gs + g - g_base) * D
                                 : k_zero + (slab * ngk + g) * D;
           const float* rc = DEV ? reinterpret_cast<const float*>(st_r4) : rope_cos + (int64_t)c * H;
           const float* rs = DEV ? reinterpret_cast<const float*>(st_r4) + H : rope_sin + (int64_t)c * H;
@@ -165,12 +171,12 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
           }
         };
         if constexpr (!DEV) load_stats();
-        // the codes of the four tokens (and, fused, their fresh key pieces)
+        // the codes of the job's tokens (and, fused, their fresh key pieces)
         // are all requested before any is used: one memory round trip per job
-        uint32_t cwl[4][2], cwh[4][2];
-        uint4 fra[4], frb[4];
+        uint32_t cwl[TOK][2], cwh[TOK][2];
+        uint4 fra[TOK], frb[TOK];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < TOK; ++i) {
           const uint8_t* row = k_codes + (slab * kC + u0 + i) * CB;
           if constexpr (BITS == 8) {
             const uint2 a = *reinterpret_cast<const uint2*>(row + j0);
@@ -188,7 +194,7 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
           }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < TOK; ++i) {
           const int u = u0 + i;
           if constexpr (DEV) {
             asm volatile("" ::: "memory");  // re-read the staged values for every token
@@ -252,11 +258,11 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
     }
 
     // ---- values
-    if constexpr (DEV) load_values();
+    if constexpr (DEV && TOK != 1) load_values();
 #pragma unroll
     for (int k = 0; k < VPT; ++k) {
       const int vj = threadIdx.x + 256 * k;
-      const int u = vj / VP, j0 = (vj % VP) * 8;
+      const int u = u_base + vj / VP, j0 = (vj % VP) * 8;
       const double sc = vsc[k], zr = vzr[k];
       float y[8];
 #pragma unroll
@@ -274,28 +280,38 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
     }
   }  // heads
   if constexpr (DEV) {
-    // one lane per token quad: delta[l][dst_row + 4q .. + 3], one 16-byte
-    // store when the quad is 16-byte aligned (dst_row and t_total multiples
-    // of 4), else four 4-byte stores (e.g. after one to three sink rows)
+    // one lane per job: delta[l][dst_row + u0 ..], for four tokens one 16-byte
+    // store when they are 16-byte aligned (dst_row and t_total multiples of 4),
+    // else 4-byte stores (e.g. after one to three sink rows)
     const int job = threadIdx.x;
     if (job < KJOBS && job % TPT == 0) {
-      const int q = job / TPT;
+      const int u0 = u_base + TOK * (job / TPT);
       const double n = (double)Hkv;
       const int64_t first = (int64_t)blockIdx.y * t_total + ch.dst_row;
-      float* dp = delta + first + 4 * q;
-      const float4 dv = make_float4((float)(1.0 - cos_sum[0] / n), (float)(1.0 - cos_sum[1] / n),
-                                    (float)(1.0 - cos_sum[2] / n), (float)(1.0 - cos_sum[3] / n));
-      if ((first & 3) == 0) {
-        *reinterpret_cast<float4*>(dp) = dv;
+      float* dp = delta + first + u0;
+      float dv[TOK];
+#pragma unroll
+      for (int i = 0; i < TOK; ++i) dv[i] = (float)(1.0 - cos_sum[i] / n);
+      if (TOK == 4 && (first & 3) == 0) {
+        *reinterpret_cast<float4*>(dp) = make_float4(dv[0], dv[TOK / 4], dv[TOK / 2], dv[TOK - 1]);
       } else {
-        dp[0] = dv.x;
-        dp[1] = dv.y;
-        dp[2] = dv.z;
-        dp[3] = dv.w;
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) dp[i] = dv[i];
       }
     }
   }
 }
+
+// A workgroup takes a whole chunk (four tokens a thread, the statistics loaded
+// once for them) when the grid has enough of them; otherwise a thread takes one
+// token and the chunk is split over 4 (d = 128) or 2 workgroups: a launch of a
+// few chunks is bound by one workgroup's chain of loads and double arithmetic,
+// which is then a quarter as long.  Measured, one token against four a thread:
+// fused, 36 chunk-layers 6.2 against 13.0 us, 252 14.8 / 17.7, 1152 61.8 / 65.1,
+// 2304 119 / 116; plain, 2 chunk-heads 3.2 / 4.6 us, 96 4.7 / 5.5, 240 8.0 / 7.5,
+// 2304 56 / 47 (its statistics are loaded per token then).
+constexpr int64_t kSplitFused = 1536, kSplitPlain = 128;
+unsigned token_splits(int head_dim) { return head_dim == 128 ? 4 : 2; }
 
 }  // namespace
 
@@ -305,13 +321,22 @@ hipError_t launch_stitch(const kvb_pool_layout& p, int32_t n_pool, const uint8_t
                          int32_t n_chunks, const float* rope_cos, const float* rope_sin,
                          int64_t t_total, kvb_dtype out_dtype, void* k_cache, void* v_cache,
                          hipStream_t s) {
-  const dim3 grid(n_chunks, p.n_layers * p.n_kv_heads), block(256);
+  const bool split = (int64_t)n_chunks * p.n_layers * p.n_kv_heads < kSplitPlain;
+  const dim3 grid(n_chunks, p.n_layers * p.n_kv_heads, split ? token_splits(p.head_dim) : 1);
+  const dim3 block(256);
   const bool bf = out_dtype == KVB_BF16;
-#define KVB_STITCH(B, D, F)                                                                       \
-  hipLaunchKernelGGL((stitch_kernel<B, D, F, false>), grid, block, 0, s, p.n_layers,             \
+#define KVB_STITCH_T(B, D, F, T)                                                                  \
+  hipLaunchKernelGGL((stitch_kernel<B, D, F, false, T>), grid, block, 0, s, p.n_layers,          \
                      p.n_kv_heads, p.k_group, p.v_group, n_pool, k_codes, k_scale, k_zero,       \
                      v_codes, v_scale, v_zero, chunks, rope_cos, rope_sin, t_total, k_cache,     \
                      v_cache, nullptr, nullptr)
+#define KVB_STITCH(B, D, F)      \
+  do {                           \
+    if (split)                   \
+      KVB_STITCH_T(B, D, F, 1);  \
+    else                         \
+      KVB_STITCH_T(B, D, F, 4);  \
+  } while (0)
   if (p.bits == 8) {
     if (p.head_dim == 128) { if (bf) KVB_STITCH(8, 128, true); else KVB_STITCH(8, 128, false); }
     else { if (bf) KVB_STITCH(8, 64, true); else KVB_STITCH(8, 64, false); }
@@ -320,6 +345,7 @@ hipError_t launch_stitch(const kvb_pool_layout& p, int32_t n_pool, const uint8_t
     else { if (bf) KVB_STITCH(4, 64, true); else KVB_STITCH(4, 64, false); }
   }
 #undef KVB_STITCH
+#undef KVB_STITCH_T
   return hipGetLastError();
 }
 
@@ -331,18 +357,27 @@ hipError_t launch_stitch_deviation(const kvb_pool_layout& p, int32_t n_pool,
                                    const float* rope_cos, const float* rope_sin, int64_t t_total,
                                    void* k_cache, void* v_cache, const uint16_t* k_fresh,
                                    float* delta, hipStream_t s) {
-  const dim3 grid(n_chunks, p.n_layers), block(256);
-#define KVB_STITCH_DEV(B, D)                                                                      \
-  hipLaunchKernelGGL((stitch_kernel<B, D, true, true>), grid, block, 0, s, p.n_layers,           \
+  const bool split = (int64_t)n_chunks * p.n_layers < kSplitFused;
+  const dim3 grid(n_chunks, p.n_layers, split ? token_splits(p.head_dim) : 1), block(256);
+#define KVB_STITCH_DEV_T(B, D, T)                                                                 \
+  hipLaunchKernelGGL((stitch_kernel<B, D, true, true, T>), grid, block, 0, s, p.n_layers,        \
                      p.n_kv_heads, p.k_group, p.v_group, n_pool, k_codes, k_scale, k_zero,       \
                      v_codes, v_scale, v_zero, chunks, rope_cos, rope_sin, t_total, k_cache,     \
                      v_cache, k_fresh, delta)
+#define KVB_STITCH_DEV(B, D)      \
+  do {                            \
+    if (split)                    \
+      KVB_STITCH_DEV_T(B, D, 1);  \
+    else                          \
+      KVB_STITCH_DEV_T(B, D, 4);  \
+  } while (0)
   if (p.bits == 8) {
     if (p.head_dim == 128) KVB_STITCH_DEV(8, 128); else KVB_STITCH_DEV(8, 64);
   } else {
     if (p.head_dim == 128) KVB_STITCH_DEV(4, 128); else KVB_STITCH_DEV(4, 64);
   }
 #undef KVB_STITCH_DEV
+#undef KVB_STITCH_DEV_T
   return hipGetLastError();
 }
 
