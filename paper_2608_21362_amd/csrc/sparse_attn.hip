@@ -1330,9 +1330,10 @@ void launch_shape(const AttnPlan& plan, int* n_wg, int* n_first) {
 // Launch shape: whole 128-query tiles, key-split 32-query tiles or balanced
 // ranges, whichever the estimate below says ends first (host arithmetic on the
 // call's sizes alone, so kvb_patch and kvb_sparse_attn_layer agree).  In
-// microseconds, fitted to 34 launches of 12 to 712 tiles over 128 to 8192 rows
+// microseconds, fitted to 35 launches of 12 to 712 tiles over 128 to 8192 rows
 // (16 query heads, 2 kv heads, d = 128; other head shapes order the same way),
-// for which the choice is never more than 4 % slower than the best shape;
+// for which the choice is at most 7 % slower than the best shape and 1 % than
+// balanced ranges;
 // b = key blocks of the longest prompt, w = tiles x b per resident workgroup,
 // r = tiles per resident workgroup:
 //  * whole tiles: a block takes 0.62 us of a workgroup alone on its CU and 0.92
@@ -1352,7 +1353,8 @@ AttnMode attn_mode(const AttnPlan& plan, int n_wg) {
   const double b = (plan.max_seq_len + kKB - 1) / kKB;
   const double r = (double)plan.n_tiles / n_wg, w = r * b;
   const double whole = 6.5 + b * (0.62 + 0.30 * fmin(r, 1.0)) * fmax(r, 1.0);
-  const double split = fmax(5.3 + 0.78 * ceil(b / kWaves), 2.3 + 21.0 * r + 0.79 * w);
+  const double split =
+      fmax(5.0 + 0.87 * ceil(b / kWaves), 2.3 + 0.06 * b + 21.0 * r + 0.79 * w);
   const double balanced = 15.0 + 0.042 * b + 29.5 * r + 0.37 * w;
   if (split <= whole && split <= balanced) return AttnMode::kSplit;
   return whole <= balanced ? AttnMode::kWhole : AttnMode::kBalanced;
