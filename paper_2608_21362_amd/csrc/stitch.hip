@@ -74,7 +74,7 @@ stitch_kernel(int32_t L, int32_t Hkv, int32_t Gk, int32_t Gv, int32_t n_pool,
       (int64_t)ch.dst_row + kC > t_total)
     return;
   const int ngk = kC / Gk, ngv = D / Gv;
-  const int u_base = (int)blockIdx.z * WT;
+  const int u_base = TOK == 4 ? 0 : (int)blockIdx.z * WT;
   // fused deviation: running cosine sum over heads of this thread's tokens
   double cos_sum[TOK] = {};
   // fused: the head's key statistics of the workgroup's groups (scale, then
