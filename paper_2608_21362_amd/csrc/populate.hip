@@ -298,8 +298,12 @@ hipError_t launch_rope_rows(int head_dim, int64_t n_outer, int64_t n_rows, int64
   return hipGetLastError();
 }
 
-// Chunk importance (Sec. 4.4): one workgroup of 1024 lanes per chunk.  Each key
-// vector is read by 8 adjacent lanes: 16-byte piece i of the vector goes to
+// Chunk importance (Sec. 4.4): workgroups of 1024 lanes, each over a slice of a
+// chunk's vectors.  One CU reads about 100 GB/s whatever its loads in flight, so
+// a chunk is dealt to up to kImpSplit workgroups until the launch has two per
+// CU; the last one to finish adds the slices' sums in slice order (imp_finish).
+// 12 chunks x 36 layers of fp64 keys (113 MB): one workgroup a chunk 96 us, 16
+// workgroups 26 us.  Each key vector is read by 8 adjacent lanes: 16-byte piece i of the vector goes to
 // lane i % 8, so every load instruction of a wave reads 8 whole 128-byte
 // segments (8 vectors).  All of a lane's pieces are requested before any is
 // summed; a lane sums its squares in piece order (double), the 8 lanes combine
@@ -309,6 +313,85 @@ hipError_t launch_rope_rows(int head_dim, int64_t n_outer, int64_t n_rows, int64
 // sums in wave order, and the chunk's share is added to importance[p].  Fixed
 // assignment and order: deterministic.
 constexpr int kImpLanes = 8;  // lanes per key vector
+
+// Meeting place of a chunk's workgroups.  The call has no workspace, so it is a
+// static device array, safe for any streams and threads: a slot belongs to the
+// address the sum is added to (calls that add to one address at the same time
+// race on it in any case) from its chunk's first finished workgroup to its last,
+// which clears it.  A chunk's workgroups look only at the 64 slots of its index
+// in the launch (one a lane), so slots run out only if 64 launches execute at
+// once; an arrival then waits for one to end.
+constexpr int kImpSplit = 16;       // most workgroups per chunk
+constexpr int kImpMaxChunks = 256;  // launches of more chunks do not split them
+struct ImpSlot {
+  unsigned long long key;  // address of the chunk's importance, 0 = free
+  unsigned int arrived;    // finished workgroups
+  unsigned int pad;
+  double part[kImpSplit];
+};
+static __device__ ImpSlot imp_slots[kImpMaxChunks][64];
+static __device__ unsigned int imp_locks[kImpMaxChunks];
+
+#define KVB_AGENT __HIP_MEMORY_SCOPE_AGENT
+
+// Slot of `key` among the 64 of chunk index p, taken if there is none yet.  Wave
+// uniform.  A slot found belongs to the caller's chunk until the caller has
+// arrived.  Slots are taken under the index's lock, so that a key is never given
+// two; its holder waits for nothing, so every wait on it ends.
+__device__ __forceinline__ ImpSlot* imp_slot(int p, unsigned long long key) {
+  ImpSlot* const row = imp_slots[p];
+  const int lane = threadIdx.x & 63;
+  auto look = [&](unsigned long long what) {
+    return __builtin_amdgcn_ballot_w64(
+        __hip_atomic_load(&row[lane].key, __ATOMIC_ACQUIRE, KVB_AGENT) == what);
+  };
+  uint64_t hit = look(key);
+  while (hit == 0) {
+    unsigned int held = 1;
+    if (lane == 0) held = __hip_atomic_exchange(&imp_locks[p], 1u, __ATOMIC_ACQUIRE, KVB_AGENT);
+    if (__builtin_amdgcn_readfirstlane(held) == 0) {
+      hit = look(key);
+      if (hit == 0 && (hit = look(0ull)) != 0 && lane == __ffsll((unsigned long long)hit) - 1)
+        __hip_atomic_store(&row[lane].key, key, __ATOMIC_RELAXED, KVB_AGENT);
+      if (lane == 0) __hip_atomic_store(&imp_locks[p], 0u, __ATOMIC_RELEASE, KVB_AGENT);
+    } else {
+      __builtin_amdgcn_s_sleep(2);
+      hit = look(key);
+    }
+  }
+  return row + (__ffsll((unsigned long long)hit) - 1);
+}
+
+// Sum of doubles that keeps the rounding errors of its additions (two-sum), so
+// that more partial sums do not round more.
+struct SumDD {
+  double s = 0.0, c = 0.0;
+  __device__ __forceinline__ void add(double x) {
+    const double t = s + x, y = t - s;
+    c += (s - (t - y)) + (x - y);
+    s = t;
+  }
+  // an infinite or NaN sum has no error term
+  __device__ __forceinline__ double value() const { return isfinite(c) ? s + c : s; }
+};
+
+// Adds this slice's sum to its chunk's; the chunk's last workgroup adds the
+// slices' sums in slice order to *importance.  Called by one whole wave.
+__device__ __forceinline__ void imp_finish(int p, int slice, int n_slices, double sum,
+                                           double inv_count, double* importance) {
+  ImpSlot* const slot = imp_slot(p, (unsigned long long)(uintptr_t)importance);
+  if ((threadIdx.x & 63) != 0) return;
+  __hip_atomic_store(&slot->part[slice], sum, __ATOMIC_RELAXED, KVB_AGENT);
+  if (__hip_atomic_fetch_add(&slot->arrived, 1u, __ATOMIC_ACQ_REL, KVB_AGENT) + 1 <
+      (unsigned)n_slices)
+    return;
+  SumDD total;
+  for (int w = 0; w < n_slices; ++w)
+    total.add(__hip_atomic_load(&slot->part[w], __ATOMIC_RELAXED, KVB_AGENT));
+  *importance += total.value() * inv_count;
+  __hip_atomic_store(&slot->arrived, 0u, __ATOMIC_RELAXED, KVB_AGENT);
+  __hip_atomic_store(&slot->key, 0ull, __ATOMIC_RELEASE, KVB_AGENT);
+}
 
 template <typename T>
 __device__ __forceinline__ double sum_sq_piece(const T* p) {  // one 16-byte piece
@@ -335,8 +418,14 @@ importance_kernel(int32_t n_vectors, double inv_count, const void* __restrict__ 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = threadIdx.x % kImpLanes;
   const T* base = reinterpret_cast<const T*>(in) + (int64_t)p * n_vectors * D;
+  // this workgroup's slice: whole rounds of 128 vectors
+  constexpr int kRound = 1024 / kImpLanes;
+  const int n_slices = gridDim.y, slice = blockIdx.y;
+  const int rounds = (n_vectors + kRound - 1) / kRound;
+  const int v_lo = (int)((int64_t)rounds * slice / n_slices) * kRound;
+  const int v_hi = min((int)((int64_t)rounds * (slice + 1) / n_slices) * kRound, n_vectors);
   double acc = 0.0;
-  for (int v = threadIdx.x / kImpLanes; v < n_vectors; v += 1024 / kImpLanes) {
+  for (int v = v_lo + threadIdx.x / kImpLanes; v < v_hi; v += kRound) {
     const T* row = base + (int64_t)v * D + sub * PER;
     double part[LP];
 #pragma unroll
@@ -352,11 +441,13 @@ importance_kernel(int32_t n_vectors, double inv_count, const void* __restrict__ 
   for (int m = 1; m < 64; m <<= 1) acc += __shfl_xor(acc, m, 64);
   if (lane == 0) wave_sum[wave] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double total = 0.0;
-    for (int w = 0; w < 16; ++w) total += wave_sum[w];
-    importance[p] += total * inv_count;
-  }
+  if (wave != 0) return;
+  SumDD total;
+  for (int w = 0; w < 16; ++w) total.add(wave_sum[w]);
+  if (n_slices > 1)
+    imp_finish(p, slice, n_slices, total.value(), inv_count, importance + p);
+  else if (lane == 0)
+    importance[p] += total.value() * inv_count;
 }
 
 hipError_t launch_kivi_quantize(const kvb_pool_layout& p, int32_t n_pool, int32_t first_layer,
@@ -403,8 +494,14 @@ hipError_t launch_chunk_importance(const kvb_pool_layout& p, int32_t n_pool, int
                                    hipStream_t s) {
   const int32_t n_vectors = n_in * p.n_kv_heads * p.chunk_len;
   const double inv_count = 1.0 / ((double)p.n_layers * p.n_kv_heads * p.chunk_len);
+  // workgroups per chunk: two per CU in the launch, each with four rounds of 128
+  // vectors or more (a slice's arrival costs about as much as two rounds)
+  int split = n_pool <= kImpMaxChunks ? 512 / n_pool : 1;
+  if (split > n_vectors / 512) split = n_vectors / 512;
+  if (split > kImpSplit) split = kImpSplit;
+  if (split < 1) split = 1;
 #define KVB_IMPORTANCE(T, D)                                                                    \
-  hipLaunchKernelGGL((importance_kernel<T, D>), dim3(n_pool), dim3(1024), 0, s, n_vectors,      \
+  hipLaunchKernelGGL((importance_kernel<T, D>), dim3(n_pool, split), dim3(1024), 0, s, n_vectors, \
                      inv_count, k_in, importance)
   if (in_dtype == KVB_F64) {
     if (p.head_dim == 128) KVB_IMPORTANCE(double, 128); else KVB_IMPORTANCE(double, 64);
