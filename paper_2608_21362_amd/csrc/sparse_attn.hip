@@ -3,13 +3,15 @@
 // Per call, on one stream:
 //
 //   patch_kernel     cache[l][h][t] <- fresh[l][h][t] for every selected row t
-//                    (both tensors, every kv head); its first workgroups build
-//                    the work decomposition when the launch uses balanced
-//                    ranges (below)
-//   v16_kernel       the fp16 copy of the patched V cache that the P.V product
-//                    takes as its operand (exact for |v| < 65536: a bf16
-//                    significand fits an fp16 one; values fp16 cannot hold are
-//                    reported in a status word)
+//                    (both tensors, every kv head) and the fp16 copy of the
+//                    patched V cache that the P.V product takes as its operand
+//                    (exact for |v| < 65536: a bf16 significand fits an fp16
+//                    one; values fp16 cannot hold are reported in a status
+//                    word); its first workgroups build the work decomposition
+//                    when the launch uses balanced ranges, or the order of the
+//                    tiles of a batch (below)
+//   v16_kernel       the fp16 copy of V as a launch of its own, for long row
+//                    lists
 //   attn_kernel      the attention itself (below); launches of few short tiles
 //                    take attn_split_kernel instead
 //   combine_kernel   merges the partial records of tiles that were cut between
@@ -916,10 +918,94 @@ __device__ __forceinline__ void build_order(
   for (int s = n + tid; s < tile_slots; s += nt) order[s] = s;  // empty slots
 }
 
+// Patch and fp16 copy of V in one pass (up to kFuseRows rows and kFuseBytes of V): a
+// workgroup owns `span` consecutive rows of one layer, all kv heads.  It marks
+// the selected ones by reading the whole list (coalesced, from L2, whatever its
+// order; a list of n rows costs n / 256 loads a thread, which is why long lists
+// keep the two launches), then takes V from the fresh tensor or the cache, writes
+// its fp16 copy and, where selected, the cache's K and V.  The separate launches
+// cost a second launch and read the patched V rows back, but stream large caches
+// better: 36 layers of 8192 rows (151 MB of V) 71 us in two launches, 75 in one;
+// of 2432 rows (45 MB) 39 and 35; 4 layers of 1667 rows, d = 64 (1.7 MB) 6.6 and
+// 5.8 with a launch less.
+constexpr int kFuseRows = 4096;
+constexpr int64_t kFuseBytes = 64 << 20;
+constexpr int kSpanMax = 64;
+
+__device__ __forceinline__ void patch_span(
+    int32_t Hkv, int32_t log2c, int64_t t_total, int32_t span_log2, int64_t l, int64_t t0,
+    const int32_t* __restrict__ rows, const int32_t* __restrict__ n_ptr, int32_t max_rows,
+    const uint16_t* kf, const uint16_t* vf, uint16_t* kc, uint16_t* vc, uint16_t* v16,
+    uint32_t* status) {
+  __shared__ uint32_t marks[kSpanMax / 32];
+  const int tid = threadIdx.x, nt = blockDim.x;  // 256
+  if (tid < kSpanMax / 32) marks[tid] = 0;
+  __syncthreads();
+  const int n_rows = (int)min((int64_t)1 << span_log2, t_total - t0);
+  constexpr int U = 8;
+  // entries are requested beside the list's length (it has room for max_rows)
+  const int n = min(*n_ptr, max_rows);
+  for (int base = 0; base < max_rows; base += U * nt) {
+    int t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = rows[min(base + u * nt + tid, max_rows - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t r = (int64_t)t[u] - t0;
+      if (base + u * nt + tid < n && r >= 0 && r < n_rows) atomicOr(&marks[r >> 5], 1u << (r & 31));
+    }
+  }
+  __syncthreads();
+  const uint64_t sel = ((uint64_t)marks[1] << 32) | marks[0];
+  // piece i of the span: head i >> (span + c bits), row, 16-byte piece of the row
+  const int total = Hkv << (span_log2 + log2c);
+  bool bad = false;
+  for (int base = 0; base < total; base += U * nt) {
+    uint4 v[U], k[U];
+    int64_t off[U];
+    bool in[U], take[U];
+    // loads are unconditional, so that all are in flight together: a piece past
+    // the span reads its last row, a key not taken the span's first piece
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + u * nt + tid;
+      const int r = (i >> log2c) & ((1 << span_log2) - 1);
+      in[u] = i < total && r < n_rows;
+      take[u] = in[u] && ((sel >> r) & 1);
+      const int h = min(i >> (span_log2 + log2c), Hkv - 1);
+      const int64_t row = (l * Hkv + h) * t_total + t0 + min(r, n_rows - 1);
+      off[u] = (row << (log2c + 3)) + 8 * (i & ((1 << log2c) - 1));
+      v[u] = *reinterpret_cast<const uint4*>((take[u] ? vf : vc) + off[u]);
+    }
+    const int64_t off0 = ((l * Hkv) * t_total + t0) << (log2c + 3);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      k[u] = *reinterpret_cast<const uint4*>(kf + (take[u] ? off[u] : off0));
+#pragma unroll
+    for (int u = 0; u < U; ++u)  // requested here, not in the branch that stores them
+      asm volatile("" ::"v"(k[u].x), "v"(k[u].y), "v"(k[u].z), "v"(k[u].w));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!in[u]) continue;
+      const uint4 a = v[u];
+      bad |= f16_out_of_range(a.x) || f16_out_of_range(a.y) || f16_out_of_range(a.z) ||
+             f16_out_of_range(a.w);
+      *reinterpret_cast<uint4*>(v16 + off[u]) = make_uint4(
+          bf16x2_to_f16x2(a.x), bf16x2_to_f16x2(a.y), bf16x2_to_f16x2(a.z), bf16x2_to_f16x2(a.w));
+      if (!take[u]) continue;
+      *reinterpret_cast<uint4*>(vc + off[u]) = a;
+      *reinterpret_cast<uint4*>(kc + off[u]) = k[u];
+    }
+  }
+  if (status != nullptr && bad) *status = 1u;
+}
+
 constexpr int kPatchRows = 4;  // row-list entries per patch wave
 
 // Patch: cache[l][h][t] <- fresh[l][h][t] for every selected row t (both
-// tensors, every kv head; one wave per kPatchRows rows).  With plan != NULL the first
+// tensors, every kv head; one wave per kPatchRows rows), or with v16 != NULL patch
+// and fp16 copy of V, one workgroup per 2^span_log2 cache rows (patch_span).  With
+// plan != NULL the first
 // n_plans workgroups build work decompositions instead: one plan over all L
 // layers (n_plans = 1), or one plan per layer (n_plans = L, plan p at
 // plan + p * plan_stride, over layer p's row set alone).  n_tiles counts the
@@ -934,7 +1020,7 @@ patch_kernel(int32_t L, int32_t Hkv, int32_t D, int64_t t_total, int32_t n_seqs,
              const int32_t* __restrict__ cu_seqlens, int32_t n_tiles, int32_t tile_slots,
              int32_t rows_per_tile, int32_t n_wg, int32_t n_first, int32_t n_wg_max,
              int32_t* __restrict__ plan, int32_t n_plans, int64_t plan_stride,
-             int32_t order_half) {
+             int32_t order_half, uint16_t* v16, uint32_t* status, int32_t span_log2) {
   // the plan builders come first: dispatched first, they start their chains of
   // dependent loads while the copying workgroups are still being dispatched
   if (plan != nullptr && (int)blockIdx.x < n_plans) {
@@ -957,6 +1043,15 @@ patch_kernel(int32_t L, int32_t Hkv, int32_t D, int64_t t_total, int32_t n_seqs,
     return;
   }
   const int64_t copy_block = (int64_t)blockIdx.x - (plan != nullptr ? n_plans : 0);
+  if (v16 != nullptr) {
+    const int64_t spans = (t_total + (1 << span_log2) - 1) >> span_log2;
+    const int64_t l = copy_block / spans, t0 = (copy_block % spans) << span_log2;
+    const int64_t set = rows_per_layer ? l : 0;
+    if (l < L)
+      patch_span(Hkv, D == 128 ? 4 : 3, t_total, span_log2, l, t0, rows + set * t_total,
+                 cu_rows + set * (n_seqs + 1) + n_seqs, max_rows, kf, vf, kc, vc, v16, status);
+    return;
+  }
   const int64_t wave = (copy_block * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
   // each wave copies kPatchRows consecutive entries of the row list, with all
@@ -1492,27 +1587,6 @@ bool ordered(const AttnPlan& plan, AttnMode mode, int n_wg, int n_seqs) {
   return mode == AttnMode::kWhole && n_seqs > 1 && n_seqs <= kOrderSeqs && plan.n_tiles > n_wg;
 }
 
-// Patch launch: copies the selected rows of n_layers layers; with plans != NULL
-// its first n_plans workgroups build the plans, or with `order` the orders of
-// the tile slots (see patch_kernel).
-void launch_patch(int n_layers, int n_kv_heads, int head_dim, int64_t t_total,
-                  const int32_t* cu_seqlens, int n_seqs, const int32_t* rows,
-                  const int32_t* cu_rows, int rows_per_layer, int max_rows,
-                  const uint16_t* k_fresh, const uint16_t* v_fresh, uint16_t* k_cache,
-                  uint16_t* v_cache, const AttnPlan& plan, int n_wg, int n_first,
-                  int32_t* plans, int n_plans, int64_t plan_stride, bool order,
-                  hipStream_t s) {
-  const int64_t waves = (int64_t)n_layers * ((max_rows + kPatchRows - 1) / kPatchRows);
-  const int64_t blocks = (waves * 64 + 255) / 256 + (plans ? n_plans : 0);
-  if (blocks > 0)
-    hipLaunchKernelGGL(patch_kernel, dim3((unsigned)blocks), dim3(256), 0, s, n_layers, n_kv_heads,
-                       head_dim, t_total, n_seqs, rows, cu_rows, rows_per_layer, max_rows, k_fresh,
-                       v_fresh, k_cache, v_cache, cu_seqlens, plan.n_tiles, plan.tile_slots,
-                       plan.rows_per_tile, n_wg, n_first, plan.n_wg_max, plans, n_plans,
-                       plan_stride,
-                       order ? ((plan.max_seq_len + kKB - 1) / kKB + 1) / 2 : 0);
-}
-
 // fp16 copy of the V cache of n_layers layers (status as for v16_kernel).
 void launch_v16(int n_layers, int n_kv_heads, int head_dim, int64_t t_total, const uint16_t* v,
                 uint16_t* v16, uint32_t* status, hipStream_t s) {
@@ -1521,6 +1595,37 @@ void launch_v16(int n_layers, int n_kv_heads, int head_dim, int64_t t_total, con
   if (blocks > 8192) blocks = 8192;
   if (blocks > 0)
     hipLaunchKernelGGL(v16_kernel, dim3((unsigned)blocks), dim3(256), 0, s, n8, v, v16, status);
+}
+
+// Patch launch: copies the selected rows of n_layers layers; with plans != NULL
+// its first n_plans workgroups build the plans, or with `order` the orders of
+// the tile slots (see patch_kernel).  With v16 also the fp16 copy of V, in the
+// same launch (patch_span) or a second one.
+void launch_patch(int n_layers, int n_kv_heads, int head_dim, int64_t t_total,
+                  const int32_t* cu_seqlens, int n_seqs, const int32_t* rows,
+                  const int32_t* cu_rows, int rows_per_layer, int max_rows,
+                  const uint16_t* k_fresh, const uint16_t* v_fresh, uint16_t* k_cache,
+                  uint16_t* v_cache, const AttnPlan& plan, int n_wg, int n_first,
+                  int32_t* plans, int n_plans, int64_t plan_stride, bool order,
+                  uint16_t* v16, uint32_t* v_status, hipStream_t s) {
+  // rows per workgroup of the one-pass form: 64, or 32 where that leaves CUs idle
+  const int span_log2 = n_layers * ((t_total + 63) / 64) >= 512 ? 6 : 5;
+  const bool fused = v16 != nullptr && max_rows <= kFuseRows &&
+                     (int64_t)n_layers * n_kv_heads * t_total * head_dim * 2 <= kFuseBytes;
+  const int64_t waves = (int64_t)n_layers * ((max_rows + kPatchRows - 1) / kPatchRows);
+  const int64_t copies = fused ? n_layers * ((t_total + (1 << span_log2) - 1) >> span_log2)
+                               : (waves * 64 + 255) / 256;
+  const int64_t blocks = copies + (plans ? n_plans : 0);
+  if (blocks > 0)
+    hipLaunchKernelGGL(patch_kernel, dim3((unsigned)blocks), dim3(256), 0, s, n_layers, n_kv_heads,
+                       head_dim, t_total, n_seqs, rows, cu_rows, rows_per_layer, max_rows, k_fresh,
+                       v_fresh, k_cache, v_cache, cu_seqlens, plan.n_tiles, plan.tile_slots,
+                       plan.rows_per_tile, n_wg, n_first, plan.n_wg_max, plans, n_plans,
+                       plan_stride,
+                       order ? ((plan.max_seq_len + kKB - 1) / kKB + 1) / 2 : 0,
+                       fused ? v16 : nullptr, v_status, span_log2);
+  if (v16 != nullptr && !fused)
+    launch_v16(n_layers, n_kv_heads, head_dim, t_total, v_cache, v16, v_status, s);
 }
 
 // Attention (and, for balanced ranges, the merge of cut tiles) over an already
@@ -1590,8 +1695,7 @@ hipError_t launch_sparse_attn(const AttnPlan& plan, int n_layers, int n_q_heads,
   if (mode != AttnMode::kBalanced && !order) wplan = nullptr;
   launch_patch(n_layers, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs, rows, cu_rows,
                rows_per_layer, max_rows, k_fresh, v_fresh, k_cache, v_cache, plan, n_wg, n_first,
-               wplan, 1, 0, order, s);
-  launch_v16(n_layers, n_kv_heads, head_dim, t_total, v_cache, v16, v_status, s);
+               wplan, 1, 0, order, v16, v_status, s);
   launch_attend(plan, n_wg, mode, n_q_heads, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs,
                 rows, cu_rows, rows_per_layer, q, k_cache, v16, softmax_scale, out_dtype, out,
                 wplan, parts, s);
@@ -1626,8 +1730,9 @@ hipError_t launch_patch_layers(const AttnPlan& layer_plan, int n_layers, int n_k
     launch_patch(n_layers, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs, rows, cu_rows,
                  rows_per_layer, max_rows, k_fresh, v_fresh, k_cache, v_cache, layer_plan, n_wg,
                  n_first, p, n_layers,
-                 (int64_t)(layer_plan_stride(layer_plan) / sizeof(int32_t)), order, s);
-  if (v_cache_f16 != nullptr)
+                 (int64_t)(layer_plan_stride(layer_plan) / sizeof(int32_t)), order, v_cache_f16,
+                 v_status, s);
+  else if (v_cache_f16 != nullptr)
     launch_v16(n_layers, n_kv_heads, head_dim, t_total, v_cache, v_cache_f16, v_status, s);
   return hipGetLastError();
 }
