@@ -77,24 +77,28 @@ rope_rows_kernel(int64_t n_outer, int64_t n_rows, int64_t n_inner, const float* 
 
 // Code of x in a group with minimum mn and range r:
 //   c = clamp(rint(((x - mn) / r) * levels), 0, levels), 0 for a constant group.
-// The double division is replaced by a product with inv = 1 / r wherever that
-// cannot change c: both forms carry at most three roundings of a value of at
-// most `levels` (255), so they differ by less than 1e-12, and rint can only
-// tell them apart within that distance of a half.  A value closer than 1e-9 to
-// a half, or not a number, takes the division; so does a range whose
-// reciprocal leaves the normal numbers (`fast` false).  r == 0 is never fast.
-__device__ __forceinline__ uint32_t quant_code(double x, double mn, double r, double inv, bool fast,
-                                               double levels) {
-  const double a = x - mn;
-  double t = (a * inv) * levels;
-  double c = rint(t);
-  if (__builtin_expect(!fast || !(fabs(t - c) < 0.5 - 1e-9), 0)) {
-    t = r != 0.0 ? (a / r) * levels : 0.0;
-    c = rint(t);
-  }
-  return (uint32_t)fmin(fmax(c, 0.0), levels);
+// The double division is replaced by a product with k = (1 / r) * levels wherever
+// that cannot change c: both forms carry at most three roundings of a value of at
+// most `levels` (255), so they differ by less than 1e-12, and rint can only tell
+// them apart within that distance of a half.  A value closer than 1e-9 to a half,
+// or not a number, is `unsure` and takes the division (slow_code); so does a range
+// whose reciprocal leaves the normal numbers (k = NaN: every value is unsure).
+// Adding 1.5 * 2^52 rounds to the nearest integer, ties to even, as rint does, and
+// leaves it in the low word; a sure value lies in [0, levels] as it is.
+__device__ __forceinline__ uint32_t sure_code(double x, double mn, double k, bool& unsure) {
+  constexpr double shift = 6755399441055744.0;
+  const double t = (x - mn) * k, u = t + shift;
+  unsure |= !(fabs(t - (u - shift)) < 0.5 - 1e-9);
+  return (uint32_t)__builtin_bit_cast(uint64_t, u);
 }
-__device__ __forceinline__ bool quant_fast(double r) { return r > 1e-290 && r < 1e290; }
+__device__ __forceinline__ uint32_t slow_code(double x, double mn, double r, double levels) {
+  const double t = r != 0.0 ? ((x - mn) / r) * levels : 0.0;
+  return (uint32_t)fmin(fmax(rint(t), 0.0), levels);
+}
+// k of a range (1 / 0 and the like included: NaN)
+__device__ __forceinline__ double code_factor(double r, double levels) {
+  return r > 1e-290 && r < 1e290 ? (1.0 / r) * levels : __builtin_nan("");
+}
 
 // N consecutive elements at p (16-byte aligned for N * sizeof(T) >= 16)
 template <typename T, int N>
@@ -115,8 +119,9 @@ __device__ __forceinline__ void load_n(const T* p, T (&x)[N]) {
 // flight together.  HBM-bound on the input.  Groups of 64 or 128 tokens meet
 // through LDS; smaller ones (SMALL) are found among the thread's own quads.
 // (One thread per group and channel pair, reading the group twice, divided
-// every value: 12 int4 chunks x 36 layers of fp64 keys, 113 MB, took 45 us;
-// this takes 23 us, 4.9 TB/s of input.)
+// every value: 12 int4 chunks x 36 layers of fp64 keys, 113 MB, took 45 us; this
+// takes 21 us, 5.3 TB/s of input, 23 while each code was clamped, converted and
+// branched on by itself.)
 template <typename T, int D, int BITS, bool SMALL>
 __global__ void __launch_bounds__(2 * D)
 quant_keys_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_in, int32_t Hkv,
@@ -182,8 +187,7 @@ quant_keys_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_in,
         mx[0][1] = fmax(mx[0][1], hi.y);
       }
     }
-    double inv[2], r[2];
-    bool fast[2];
+    double k[2], r[2];
 #pragma unroll
     for (int u = 0; u < TT; ++u) {
       const int q = SMALL ? u / 4 : 0;
@@ -192,8 +196,7 @@ quant_keys_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_in,
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           r[e] = mx[q][e] - mn[q][e];
-          fast[e] = quant_fast(r[e]);
-          inv[e] = 1.0 / r[e];
+          k[e] = code_factor(r[e], levels);
         }
         if (first) {
           const int64_t st = (slab * n_groups + (u0 + u) / Gk) * D + j0;
@@ -203,8 +206,13 @@ quant_keys_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_in,
           *reinterpret_cast<float2*>(zero + st) = make_float2((float)mn[q][0], (float)mn[q][1]);
         }
       }
-      const uint32_t c0 = quant_code((double)x[u][0], mn[q][0], r[0], inv[0], fast[0], levels);
-      const uint32_t c1 = quant_code((double)x[u][1], mn[q][1], r[1], inv[1], fast[1], levels);
+      bool unsure = false;
+      uint32_t c0 = sure_code((double)x[u][0], mn[q][0], k[0], unsure);
+      uint32_t c1 = sure_code((double)x[u][1], mn[q][1], k[1], unsure);
+      if (__builtin_expect(unsure, 0)) {
+        c0 = slow_code((double)x[u][0], mn[q][0], r[0], levels);
+        c1 = slow_code((double)x[u][1], mn[q][1], r[1], levels);
+      }
       uint8_t* row = codes + (slab * C + u0 + u) * CB;
       if constexpr (BITS == 8)
         *reinterpret_cast<uint16_t*>(row + j0) = (uint16_t)(c0 | (c1 << 8));
@@ -230,13 +238,16 @@ quant_values_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_i
   constexpr double levels = (double)((1 << BITS) - 1);
   const int n_groups = D / Gv;
   const int j0 = (threadIdx.x % LPT) * 8;
-  // whole workgroups step over tokens: every lane of a token's group is active
-  for (int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPT; row < n_slabs * C;
-       row += (int64_t)gridDim.x * 256 / LPT) {
-    const int64_t s = row / C;  // (p, layer of the input, h)
+  // a workgroup steps over whole token groups of one slab: every lane of a
+  // token's group is active, and the slab's indices are found once for all of them
+  constexpr int TW = 256 / LPT, PER = C / TW;  // tokens per workgroup, steps per slab
+  for (int64_t step = blockIdx.x; step < n_slabs * PER; step += gridDim.x) {
+    const int64_t s = step / PER;  // (p, layer of the input, h)
     const int64_t pl = s / Hkv;
+    const int u = (int)(step % PER) * TW + (int)threadIdx.x / LPT;
+    const int64_t row = s * C + u;
     const int64_t out_row =
-        (((pl / n_in) * L + first_layer + pl % n_in) * Hkv + s % Hkv) * C + row % C;
+        (((pl / n_in) * L + first_layer + pl % n_in) * Hkv + s % Hkv) * C + u;
     T x[8];
     load_n<T, 8>(in + row * D + j0, x);
     double mn = INFINITY, mx = -INFINITY;
@@ -249,12 +260,18 @@ quant_values_kernel(int64_t n_slabs, int32_t L, int32_t first_layer, int32_t n_i
       mn = fmin(mn, __shfl_xor(mn, m, 64));
       mx = fmax(mx, __shfl_xor(mx, m, 64));
     }
-    const double r = mx - mn, inv = 1.0 / r;
-    const bool fast = quant_fast(r);
+    const double r = mx - mn, k = code_factor(r, levels);
+    uint32_t c[8];
+    bool unsure = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) c[e] = sure_code((double)x[e], mn, k, unsure);
+    if (__builtin_expect(unsure, 0)) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c[e] = slow_code((double)x[e], mn, r, levels);
+    }
     uint32_t w[BITS == 8 ? 2 : 1] = {};
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      w[e * BITS / 32] |= quant_code((double)x[e], mn, r, inv, fast, levels) << (e * BITS % 32);
+    for (int e = 0; e < 8; ++e) w[e * BITS / 32] |= c[e] << (e * BITS % 32);
     uint8_t* dst = codes + out_row * CB + j0 * BITS / 8;
     if constexpr (BITS == 8)
       *reinterpret_cast<uint2*>(dst) = make_uint2(w[0], w[1]);
