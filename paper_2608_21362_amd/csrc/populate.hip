@@ -395,7 +395,7 @@ struct SumDD {
 // Adds this slice's sum to its chunk's; the chunk's last workgroup adds the
 // slices' sums in slice order to *importance.  Called by one whole wave.
 __device__ __forceinline__ void imp_finish(int p, int slice, int n_slices, double sum,
-                                           double inv_count, double* importance) {
+                                           double count, double* importance) {
   ImpSlot* const slot = imp_slot(p, (unsigned long long)(uintptr_t)importance);
   if ((threadIdx.x & 63) != 0) return;
   __hip_atomic_store(&slot->part[slice], sum, __ATOMIC_RELAXED, KVB_AGENT);
@@ -405,7 +405,7 @@ __device__ __forceinline__ void imp_finish(int p, int slice, int n_slices, doubl
   SumDD total;
   for (int w = 0; w < n_slices; ++w)
     total.add(__hip_atomic_load(&slot->part[w], __ATOMIC_RELAXED, KVB_AGENT));
-  *importance += total.value() * inv_count;
+  *importance += total.value() / count;
   __hip_atomic_store(&slot->arrived, 0u, __ATOMIC_RELAXED, KVB_AGENT);
   __hip_atomic_store(&slot->key, 0ull, __ATOMIC_RELEASE, KVB_AGENT);
 }
@@ -424,7 +424,7 @@ __device__ __forceinline__ double sum_sq_piece(const T* p) {  // one 16-byte pie
 
 template <typename T, int D>
 __global__ void __launch_bounds__(1024)
-importance_kernel(int32_t n_vectors, double inv_count, const void* __restrict__ in,
+importance_kernel(int32_t n_vectors, double count, const void* __restrict__ in,
                   double* __restrict__ importance) {
   constexpr int PER = 16 / (int)sizeof(T);    // elements per piece
   constexpr int NP = D / PER;                 // pieces per vector
@@ -462,9 +462,9 @@ importance_kernel(int32_t n_vectors, double inv_count, const void* __restrict__ 
   SumDD total;
   for (int w = 0; w < 16; ++w) total.add(wave_sum[w]);
   if (n_slices > 1)
-    imp_finish(p, slice, n_slices, total.value(), inv_count, importance + p);
+    imp_finish(p, slice, n_slices, total.value(), count, importance + p);
   else if (lane == 0)
-    importance[p] += total.value() * inv_count;
+    importance[p] += total.value() / count;
 }
 
 hipError_t launch_kivi_quantize(const kvb_pool_layout& p, int32_t n_pool, int32_t first_layer,
@@ -510,7 +510,7 @@ hipError_t launch_chunk_importance(const kvb_pool_layout& p, int32_t n_pool, int
                                    kvb_dtype in_dtype, const void* k_in, double* importance,
                                    hipStream_t s) {
   const int32_t n_vectors = n_in * p.n_kv_heads * p.chunk_len;
-  const double inv_count = 1.0 / ((double)p.n_layers * p.n_kv_heads * p.chunk_len);
+  const double count = (double)p.n_layers * p.n_kv_heads * p.chunk_len;
   // workgroups per chunk: two per CU in the launch, each with four rounds of 128
   // vectors or more (a slice's arrival costs about as much as two rounds)
   int split = n_pool <= kImpMaxChunks ? 512 / n_pool : 1;
@@ -519,7 +519,7 @@ hipError_t launch_chunk_importance(const kvb_pool_layout& p, int32_t n_pool, int
   if (split < 1) split = 1;
 #define KVB_IMPORTANCE(T, D)                                                                    \
   hipLaunchKernelGGL((importance_kernel<T, D>), dim3(n_pool, split), dim3(1024), 0, s, n_vectors, \
-                     inv_count, k_in, importance)
+                     count, k_in, importance)
   if (in_dtype == KVB_F64) {
     if (p.head_dim == 128) KVB_IMPORTANCE(double, 128); else KVB_IMPORTANCE(double, 64);
   } else {
