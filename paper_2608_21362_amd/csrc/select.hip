@@ -448,7 +448,7 @@ pack_kernel(int64_t t_total, const int32_t* __restrict__ cu_seqlens, int32_t n_s
     const int32_t c = i < n_seqs ? cnt[i] : 0;
     const uint32_t incl = wave_incl((uint32_t)c);
     if (b == 0 && tid < 64 && i < n_seqs) cu[i + 1] = acc + (int32_t)incl;
-    const int before = min(b - base, 64);  // prompts of this round before b
+    const int before = min(b - base, 64);  // prompts of these 64 before b
     if (before > 0) off += (uint32_t)__builtin_amdgcn_readlane((int)incl, before - 1);
     acc += __builtin_amdgcn_readlane((int)incl, 63);
   }

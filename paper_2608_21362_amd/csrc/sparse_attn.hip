@@ -1003,14 +1003,16 @@ __device__ __forceinline__ void patch_span(
 constexpr int kPatchRows = 4;  // row-list entries per patch wave
 
 // Patch: cache[l][h][t] <- fresh[l][h][t] for every selected row t (both
-// tensors, every kv head; one wave per kPatchRows rows), or with v16 != NULL patch
-// and fp16 copy of V, one workgroup per 2^span_log2 cache rows (patch_span).  With
+// tensors, every kv head; one wave per kPatchRows rows), or with SPAN patch and
+// fp16 copy of V, one workgroup per 2^span_log2 cache rows (patch_span; a kernel of
+// its own, since it takes twice the registers).  With
 // plan != NULL the first
 // n_plans workgroups build work decompositions instead: one plan over all L
 // layers (n_plans = 1), or one plan per layer (n_plans = L, plan p at
 // plan + p * plan_stride, over layer p's row set alone).  n_tiles counts the
 // tiles of one plan.  With order_half > 0 they build the order of the tile slots
 // (build_order) where a plan keeps its prefix.
+template <bool SPAN>
 __global__ void __launch_bounds__(256)
 patch_kernel(int32_t L, int32_t Hkv, int32_t D, int64_t t_total, int32_t n_seqs,
              const int32_t* __restrict__ rows, const int32_t* __restrict__ cu_rows,
@@ -1043,7 +1045,7 @@ patch_kernel(int32_t L, int32_t Hkv, int32_t D, int64_t t_total, int32_t n_seqs,
     return;
   }
   const int64_t copy_block = (int64_t)blockIdx.x - (plan != nullptr ? n_plans : 0);
-  if (v16 != nullptr) {
+  if constexpr (SPAN) {
     const int64_t spans = (t_total + (1 << span_log2) - 1) >> span_log2;
     const int64_t l = copy_block / spans, t0 = (copy_block % spans) << span_log2;
     const int64_t set = rows_per_layer ? l : 0;
@@ -1617,13 +1619,13 @@ void launch_patch(int n_layers, int n_kv_heads, int head_dim, int64_t t_total,
                                : (waves * 64 + 255) / 256;
   const int64_t blocks = copies + (plans ? n_plans : 0);
   if (blocks > 0)
-    hipLaunchKernelGGL(patch_kernel, dim3((unsigned)blocks), dim3(256), 0, s, n_layers, n_kv_heads,
-                       head_dim, t_total, n_seqs, rows, cu_rows, rows_per_layer, max_rows, k_fresh,
-                       v_fresh, k_cache, v_cache, cu_seqlens, plan.n_tiles, plan.tile_slots,
-                       plan.rows_per_tile, n_wg, n_first, plan.n_wg_max, plans, n_plans,
-                       plan_stride,
-                       order ? ((plan.max_seq_len + kKB - 1) / kKB + 1) / 2 : 0,
-                       fused ? v16 : nullptr, v_status, span_log2);
+    hipLaunchKernelGGL(fused ? patch_kernel<true> : patch_kernel<false>, dim3((unsigned)blocks),
+                       dim3(256), 0, s, n_layers, n_kv_heads, head_dim, t_total, n_seqs, rows,
+                       cu_rows, rows_per_layer, max_rows, k_fresh, v_fresh, k_cache, v_cache,
+                       cu_seqlens, plan.n_tiles, plan.tile_slots, plan.rows_per_tile, n_wg,
+                       n_first, plan.n_wg_max, plans, n_plans, plan_stride,
+                       order ? ((plan.max_seq_len + kKB - 1) / kKB + 1) / 2 : 0, v16, v_status,
+                       span_log2);
   if (v16 != nullptr && !fused)
     launch_v16(n_layers, n_kv_heads, head_dim, t_total, v_cache, v16, v_status, s);
 }
