@@ -194,11 +194,12 @@ kvb_status kvb_kivi_quantize(const kvb_pool_layout* pool, int32_t n_pool, int32_
  * takes); importance: f64 [n_pool], ACCUMULATED: every call adds its layers'
  * share (sum of their norms / (L Hkv C)), so calls over disjoint layer sets
  * starting from zero leave the mean over all layers.  Double arithmetic; the
- * order of the sums is fixed (deterministic), so it can differ from a plain
- * left-to-right sum in the last bits.  Calls that add to the same elements of
- * importance must be ordered (one stream, or events); calls on different arrays
- * may overlap.  For callers that rank chunks for eviction; not part of the timed
- * path.
+ * order of the sums is fixed by n_in and the pool (deterministic, and the same
+ * for a chunk whatever other chunks the call takes), so it can differ from a
+ * plain left-to-right sum in the last bits.  Calls that add to the same elements
+ * of importance must be ordered (one stream, or events), else a share may be
+ * lost (later calls are not affected); calls on different arrays may overlap.
+ * For callers that rank chunks for eviction; not part of the timed path.
  * Errors: KVB_EINVAL, KVB_EUNSUPPORTED (head_dim, bits, chunk_len as in
  * kvb_pool_layout). */
 kvb_status kvb_chunk_importance(const kvb_pool_layout* pool, int32_t n_pool, int32_t n_in,

@@ -316,35 +316,40 @@ hipError_t launch_rope_rows(int head_dim, int64_t n_outer, int64_t n_rows, int64
 }
 
 // Chunk importance (Sec. 4.4): workgroups of 1024 lanes, each over a slice of a
-// chunk's vectors.  One CU reads about 100 GB/s whatever its loads in flight, so
-// a chunk is dealt to up to kImpSplit workgroups until the launch has two per
-// CU; the last one to finish adds the slices' sums in slice order (imp_finish).
-// 12 chunks x 36 layers of fp64 keys (113 MB): one workgroup a chunk 96 us, 16
-// workgroups 26 us.  Each key vector is read by 8 adjacent lanes: 16-byte piece i of the vector goes to
+// chunk's vectors; a chunk is dealt to up to kImpSplit of them (imp_split), and the
+// last one to finish adds the slices' sums (imp_finish).  12 chunks x 36 layers of
+// fp64 keys (113 MB): one workgroup a chunk 96 us, eight 24.  Each key
+// vector is read by 8 adjacent lanes: 16-byte piece i of the vector goes to
 // lane i % 8, so every load instruction of a wave reads 8 whole 128-byte
 // segments (8 vectors).  All of a lane's pieces are requested before any is
 // summed; a lane sums its squares in piece order (double), the 8 lanes combine
 // theirs with a fixed xor tree (every level adds two values, so all 8 end with
-// the same bits), and the vector's first lane adds the norm to its running
-// sum.  The lanes' sums are combined with a fixed xor-shuffle tree, the 16 wave
-// sums in wave order, and the chunk's share is added to importance[p].  Fixed
-// assignment and order: deterministic.
+// the same bits), and one of them, another for each vector, adds the norm to its
+// running sum: the square root and the addition run once for eight vectors of a
+// group.  From there on every sum keeps its rounding errors (SumDD) and the chunk's
+// is rounded once at the end, so that it is the same however the chunk was dealt
+// (but for a sum within some 2^-40 of a last place of the middle of two doubles).
 constexpr int kImpLanes = 8;  // lanes per key vector
 
 // Meeting place of a chunk's workgroups.  The call has no workspace, so it is a
-// static device array, safe for any streams and threads: a slot belongs to the
-// address the sum is added to (calls that add to one address at the same time
-// race on it in any case) from its chunk's first finished workgroup to its last,
-// which clears it.  A chunk's workgroups look only at the 64 slots of its index
-// in the launch (one a lane), so slots run out only if 64 launches execute at
-// once; an arrival then waits for one to end.
-constexpr int kImpSplit = 16;       // most workgroups per chunk
-constexpr int kImpMaxChunks = 256;  // launches of more chunks do not split them
+// static device array, safe for any streams and threads: a slot belongs to one
+// dispatch (its packet's address, which a queue uses again only after a round of
+// its whole ring) from its chunk's first finished workgroup to its last, which
+// clears it.  Every workgroup of the dispatch arrives exactly once, so no call,
+// whatever it overlaps with or adds to, leaves a slot taken or finds one of
+// another's.  A chunk's workgroups look only at the 64 slots of its index in the launch (one a
+// lane), so slots run out only if 64 dispatches hold one at once; an arrival then
+// waits for one of them to end.  That wait ends: all of them but those that are
+// still being dispatched (at most one per hardware queue, of which a process has
+// at most 32) have every workgroup on the chip, and none of these waits.
+constexpr int kImpSplit = 16;    // most workgroups per chunk
+constexpr int kImpMaxWg = 256;   // most workgroups of a launch that splits chunks
+constexpr int kImpMaxChunks = kImpMaxWg / 2;  // most chunks that it has
 struct ImpSlot {
-  unsigned long long key;  // address of the chunk's importance, 0 = free
+  unsigned long long key;  // address of the dispatch packet, 0 = free
   unsigned int arrived;    // finished workgroups
   unsigned int pad;
-  double part[kImpSplit];
+  double part[kImpSplit][2];  // a slice's sum and its rounding errors
 };
 static __device__ ImpSlot imp_slots[kImpMaxChunks][64];
 static __device__ unsigned int imp_locks[kImpMaxChunks];
@@ -379,35 +384,54 @@ __device__ __forceinline__ ImpSlot* imp_slot(int p, unsigned long long key) {
   return row + (__ffsll((unsigned long long)hit) - 1);
 }
 
-// Sum of doubles that keeps the rounding errors of its additions (two-sum), so
-// that more partial sums do not round more.
+// Sum of doubles that keeps the rounding errors of its additions (two-sum): about
+// 2^-104 relative, whatever the order.
 struct SumDD {
   double s = 0.0, c = 0.0;
-  __device__ __forceinline__ void add(double x) {
+  __device__ __forceinline__ void add(double x, double xc = 0.0) {
     const double t = s + x, y = t - s;
-    c += (s - (t - y)) + (x - y);
+    c = (c + xc) + ((s - (t - y)) + (x - y));
     s = t;
+  }
+  // sum over N adjacent lanes by a fixed xor tree (each ends with the same bits)
+  template <int N>
+  __device__ __forceinline__ void add_lanes() {
+#pragma unroll
+    for (int m = 1; m < N; m <<= 1) {
+      const double x = __shfl_xor(s, m, 64), xc = __shfl_xor(c, m, 64);
+      add(x, xc);
+    }
   }
   // an infinite or NaN sum has no error term
   __device__ __forceinline__ double value() const { return isfinite(c) ? s + c : s; }
 };
 
-// Adds this slice's sum to its chunk's; the chunk's last workgroup adds the
-// slices' sums in slice order to *importance.  Called by one whole wave.
-__device__ __forceinline__ void imp_finish(int p, int slice, int n_slices, double sum,
-                                           double count, double* importance) {
-  ImpSlot* const slot = imp_slot(p, (unsigned long long)(uintptr_t)importance);
-  if ((threadIdx.x & 63) != 0) return;
-  __hip_atomic_store(&slot->part[slice], sum, __ATOMIC_RELAXED, KVB_AGENT);
-  if (__hip_atomic_fetch_add(&slot->arrived, 1u, __ATOMIC_ACQ_REL, KVB_AGENT) + 1 <
-      (unsigned)n_slices)
-    return;
-  SumDD total;
-  for (int w = 0; w < n_slices; ++w)
-    total.add(__hip_atomic_load(&slot->part[w], __ATOMIC_RELAXED, KVB_AGENT));
-  *importance += total.value() / count;
-  __hip_atomic_store(&slot->arrived, 0u, __ATOMIC_RELAXED, KVB_AGENT);
-  __hip_atomic_store(&slot->key, 0ull, __ATOMIC_RELEASE, KVB_AGENT);
+// Leaves this slice's sum in its chunk's slot.  True, with the chunk's sum, for the
+// chunk's last workgroup (both in the first kImpSplit lanes).  Called by one whole wave.
+__device__ __forceinline__ bool imp_finish(int p, int slice, int n_slices, SumDD* sum) {
+  const int lane = threadIdx.x & 63;
+  ImpSlot* const slot =
+      imp_slot(p, (unsigned long long)(uintptr_t)__builtin_amdgcn_dispatch_ptr());
+  unsigned int before = 0;
+  if (lane == 0) {
+    __hip_atomic_store(&slot->part[slice][0], sum->s, __ATOMIC_RELAXED, KVB_AGENT);
+    __hip_atomic_store(&slot->part[slice][1], sum->c, __ATOMIC_RELAXED, KVB_AGENT);
+    before = __hip_atomic_fetch_add(&slot->arrived, 1u, __ATOMIC_ACQ_REL, KVB_AGENT);
+  }
+  if (__builtin_amdgcn_readfirstlane(before) + 1 < (unsigned)n_slices) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  *sum = SumDD();
+  if (lane < n_slices)
+    sum->add(__hip_atomic_load(&slot->part[lane][0], __ATOMIC_RELAXED, KVB_AGENT),
+             __hip_atomic_load(&slot->part[lane][1], __ATOMIC_RELAXED, KVB_AGENT));
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // every lane's loads before the slot is free
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) {
+    __hip_atomic_store(&slot->arrived, 0u, __ATOMIC_RELAXED, KVB_AGENT);
+    __hip_atomic_store(&slot->key, 0ull, __ATOMIC_RELEASE, KVB_AGENT);
+  }
+  sum->add_lanes<kImpSplit>();
+  return true;
 }
 
 template <typename T>
@@ -430,7 +454,7 @@ importance_kernel(int32_t n_vectors, double count, const void* __restrict__ in,
   constexpr int NP = D / PER;                 // pieces per vector
   constexpr int LP = NP / kImpLanes;          // pieces per lane
   static_assert(LP >= 1 && NP % kImpLanes == 0, "a vector spans whole pieces of every lane");
-  __shared__ double wave_sum[16];
+  __shared__ double wave_sum[16][2];
   const int p = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = threadIdx.x % kImpLanes;
@@ -441,7 +465,9 @@ importance_kernel(int32_t n_vectors, double count, const void* __restrict__ in,
   const int rounds = (n_vectors + kRound - 1) / kRound;
   const int v_lo = (int)((int64_t)rounds * slice / n_slices) * kRound;
   const int v_hi = min((int)((int64_t)rounds * (slice + 1) / n_slices) * kRound, n_vectors);
-  double acc = 0.0;
+  SumDD acc;
+  double mine = 0.0;  // squared norm of one of this group's last eight vectors
+  int i = 0;
   for (int v = v_lo + threadIdx.x / kImpLanes; v < v_hi; v += kRound) {
     const T* row = base + (int64_t)v * D + sub * PER;
     double part[LP];
@@ -452,19 +478,25 @@ importance_kernel(int32_t n_vectors, double count, const void* __restrict__ in,
     for (int j = 0; j < LP; ++j) ss += part[j];
 #pragma unroll
     for (int m = 1; m < kImpLanes; m <<= 1) ss += __shfl_xor(ss, m, 64);
-    if (sub == 0) acc += sqrt(ss);
+    if (sub == (i & (kImpLanes - 1))) mine = ss;
+    if ((++i & (kImpLanes - 1)) == 0) {
+      acc.add(sqrt(mine));
+      mine = 0.0;
+    }
   }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) acc += __shfl_xor(acc, m, 64);
-  if (lane == 0) wave_sum[wave] = acc;
+  acc.add(sqrt(mine));
+  acc.add_lanes<64>();
+  if (lane == 0) {
+    wave_sum[wave][0] = acc.s;
+    wave_sum[wave][1] = acc.c;
+  }
   __syncthreads();
   if (wave != 0) return;
   SumDD total;
-  for (int w = 0; w < 16; ++w) total.add(wave_sum[w]);
-  if (n_slices > 1)
-    imp_finish(p, slice, n_slices, total.value(), count, importance + p);
-  else if (lane == 0)
-    importance[p] += total.value() / count;
+  if (lane < 16) total.add(wave_sum[lane][0], wave_sum[lane][1]);
+  total.add_lanes<16>();
+  if (n_slices > 1 && !imp_finish(p, slice, n_slices, &total)) return;
+  if (lane == 0) importance[p] += total.value() / count;
 }
 
 hipError_t launch_kivi_quantize(const kvb_pool_layout& p, int32_t n_pool, int32_t first_layer,
@@ -506,17 +538,40 @@ hipError_t launch_kivi_quantize(const kvb_pool_layout& p, int32_t n_pool, int32_
   return hipGetLastError();
 }
 
+// Workgroups per chunk: at most one per CU, and what an estimate says ends first,
+// in us.  A CU reads about 80 GB/s of keys that the last-level cache holds and 50
+// from HBM whatever its loads in flight, the chip 6 TB/s (the longer of the two,
+// and a little more where they are alike); a workgroup's arrival at the meeting
+// place (cache write-back and atomics, one after another on an XCD) holds the
+// launch up by 0.05 us, and the last one's by 2, so that many chunks, or small
+// ones, are better left whole.  One workgroup a chunk, this rule and up to 512 workgroups a launch: 36 layers
+// of fp64 keys, d = 128, 12 chunks 96 / 24 / 27 us, 40 175 / 73 / 85, 100 202 / 168 /
+// 187, 256 400 / 399 / 427; 12 layers of fp32, d = 64, 64 17 / 17 / 27, 170 21 / 21 /
+// 47.  A slice has four rounds of 128 vectors or more, a chunk that is split 16
+// (8 chunks of 8 rounds, fp32, d = 64: 7.0 us whole, 8.6 in two).
+static int imp_split(int32_t n_pool, int32_t n_vectors, size_t vector_bytes) {
+  const double chunk = (double)n_vectors * vector_bytes, total = chunk * n_pool;
+  const double alone = chunk / (total < 250e6 ? 80e3 : 50e3), all = total / 6e6;
+  int split = 1;
+  double best = INFINITY;
+  for (int k = 1; k <= kImpSplit; ++k) {
+    if (k > 1 && (n_vectors < 2048 || k > n_vectors / 512 || (int64_t)n_pool * k > kImpMaxWg)) break;
+    const double r = alone / k;
+    const double t = sqrt(sqrt(all * all * all * all + r * r * r * r)) + (k > 1 ? 2.0 + 0.05 * n_pool * k : 0.0);
+    if (t < best) {
+      best = t;
+      split = k;
+    }
+  }
+  return split;
+}
+
 hipError_t launch_chunk_importance(const kvb_pool_layout& p, int32_t n_pool, int32_t n_in,
                                    kvb_dtype in_dtype, const void* k_in, double* importance,
                                    hipStream_t s) {
   const int32_t n_vectors = n_in * p.n_kv_heads * p.chunk_len;
   const double count = (double)p.n_layers * p.n_kv_heads * p.chunk_len;
-  // workgroups per chunk: two per CU in the launch, each with four rounds of 128
-  // vectors or more (a slice's arrival costs about as much as two rounds)
-  int split = n_pool <= kImpMaxChunks ? 512 / n_pool : 1;
-  if (split > n_vectors / 512) split = n_vectors / 512;
-  if (split > kImpSplit) split = kImpSplit;
-  if (split < 1) split = 1;
+  const int split = imp_split(n_pool, n_vectors, (size_t)p.head_dim * (in_dtype == KVB_F64 ? 8 : 4));
 #define KVB_IMPORTANCE(T, D)                                                                    \
   hipLaunchKernelGGL((importance_kernel<T, D>), dim3(n_pool, split), dim3(1024), 0, s, n_vectors, \
                      count, k_in, importance)

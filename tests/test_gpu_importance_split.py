@@ -1,9 +1,10 @@
 """GPU chunk importance where several workgroups share a chunk: vector counts
-at the least a slice takes, not divisible by the slices, the most slices a
-chunk is given, chunk counts around the splitting rule's edges, and repeated
+at the least a split chunk has, not divisible by the workgroups, the most
+workgroups a chunk is given, chunk counts on both sides of the rule, and repeated
 calls (each starts on what the last one left in the meeting place) on one and
 on two streams at once.  Against the oracle at relative 1e-12 (64-bit sums in
-another order); repeated calls give the same bits."""
+another order); repeated calls, and calls with other chunks beside, give the
+same bits."""
 import sys
 
 import numpy as np
@@ -14,13 +15,17 @@ from oracle import importance as oimp
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [  # (chunks, layers, kv heads, head dim, dtype): 128 * layers * heads vectors a chunk
-    (1, 8, 1, 64, np.float32),     # 2 slices
-    (1, 36, 2, 64, np.float32),    # 16 slices of 4 or 5 rounds
-    (3, 11, 1, 128, np.float64),   # 11 rounds over 2 slices
-    (40, 7, 2, 64, np.float32),    # 3 slices of 4 or 5 rounds
-    (256, 4, 2, 64, np.float32),   # 2 slices, the most chunks that are split
-    (257, 4, 2, 64, np.float32),   # one workgroup a chunk
+SHAPES = [  # (chunks, layers, kv heads, head dim, dtype): a round of 128 vectors per layer and head
+    (1, 8, 1, 64, np.float32),     # 8 rounds: one workgroup
+    (1, 15, 1, 128, np.float64),   # the most that are never split
+    (1, 16, 1, 64, np.float32),    # 4 workgroups of 4 rounds
+    (1, 36, 2, 64, np.float32),    # 16 workgroups of 4 or 5 rounds
+    (3, 17, 1, 128, np.float64),   # 17 rounds over 4 workgroups
+    (40, 17, 1, 128, np.float64),  # 17 rounds over 2 workgroups
+    (3, 11, 1, 128, np.float64),
+    (40, 7, 2, 64, np.float32),
+    (256, 4, 2, 64, np.float32),
+    (257, 4, 2, 64, np.float32),
 ]
 
 
@@ -54,3 +59,68 @@ def test_importance_split(shape):
     torch.cuda.synchronize()
     got, a, b = (x.cpu().numpy()[:P] for x in (out[0][0], out[0][1], out[1][1]))
     assert np.array_equal(got, a + b)
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64], ids=lambda t: np.dtype(t).name)
+def test_importance_same_bits_in_any_batch(dt):
+    """A chunk's importance does not depend on the chunks beside it: alone, and in
+    launches that give a chunk nine workgroups and fewer, down to one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_21362_amd import kvb
+
+    L, H, d, P = 36, 1, 64, 257
+    print(f"[importance-batch] {np.dtype(dt).name}", file=sys.stderr, flush=True)
+    g = torch.Generator("cuda").manual_seed(3)
+    keys = torch.randn((P, L, H, 128, d), generator=g, device="cuda", dtype=torch.float64)
+    keys = (keys * torch.exp(torch.randn((P, 1, 1, 1, d), generator=g, device="cuda"))).to(
+        torch.float64 if dt == np.float64 else torch.float32)
+    pool = kvb.pool_layout(L, H, d, 8, 128, d)
+    kdt = kvb.KVB_F64 if dt == np.float64 else kvb.KVB_F32
+
+    def run(n):
+        out = torch.zeros(n + (n & 1), dtype=torch.float64, device="cuda")
+        kvb.kvb_chunk_importance(pool, n, L, kdt, keys[:n].contiguous(), out)
+        torch.cuda.synchronize()
+        return out.cpu().numpy()[:n]
+
+    alone = run(1)
+    whole = run(P)
+    np.testing.assert_allclose(whole[:2], oimp.chunk_importance(keys[:2].cpu().numpy()), rtol=1e-12)
+    for n in (1, 2, 5, 10, 20, 30, 42, 73, 256):
+        assert np.array_equal(run(n).view(np.uint64), whole[:n].view(np.uint64)), n
+    assert alone[0] == whole[0]
+
+
+def test_importance_after_unordered_calls():
+    """Calls that add to one address at the same time may lose a share, but leave
+    nothing behind: the ordered calls that follow are exact, also after more of
+    them than a chunk index has meeting places."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_21362_amd import kvb
+
+    L, H, d = 36, 1, 64
+    print("[importance-unordered] 2 streams", file=sys.stderr, flush=True)
+    rng = np.random.default_rng(5)
+    k = rng.standard_normal((1, L, H, 128, d)).astype(np.float32)
+    few = [torch.from_numpy(np.ascontiguousarray(k[:, :n])).cuda() for n in (36, 16, 20)]
+    pool = kvb.pool_layout(L, H, d, 8, 128, d)
+    out = torch.zeros(2, dtype=torch.float64, device="cuda")
+    ref = torch.zeros(2, dtype=torch.float64, device="cuda")
+    kvb.kvb_chunk_importance(pool, 1, L, kvb.KVB_F32, few[0], ref)
+    streams = [torch.cuda.Stream() for _ in few]
+    torch.cuda.synchronize()
+    for _ in range(100):  # 9, 4 and 5 workgroups a chunk
+        for t, st in zip(few, streams):
+            kvb.kvb_chunk_importance(pool, 1, t.shape[1], kvb.KVB_F32, t, out, st.cuda_stream)
+    torch.cuda.synchronize()
+    for t in few:
+        out.zero_()
+        kvb.kvb_chunk_importance(pool, 1, t.shape[1], kvb.KVB_F32, t, out)
+        torch.cuda.synchronize()
+        n = t.shape[1]
+        want = oimp.chunk_importance(k[:, :n])[0] * n / L
+        np.testing.assert_allclose(out.cpu().numpy()[0], want, rtol=1e-12, atol=0)
+        if n == L:
+            assert out[0] == ref[0]
