@@ -1584,9 +1584,19 @@ AttnMode attn_mode(const AttnPlan& plan, int n_wg) {
 
 // Whether a launch of whole tiles takes its slots in the order of build_order:
 // with one prompt, or every tile resident at once, the reversed numbering does
-// as well; the order's builder takes up to kOrderSeqs prompts.
-bool ordered(const AttnPlan& plan, AttnMode mode, int n_wg, int n_seqs) {
-  return mode == AttnMode::kWhole && n_seqs > 1 && n_seqs <= kOrderSeqs && plan.n_tiles > n_wg;
+// as well; the order's builder takes up to kOrderSeqs prompts.  Launches of one
+// layer gain from it at every size tried (5 prompts of 663 rows, 32/1 heads: call
+// 48.0 -> 42.4 us; 2 prompts of up to 8.2K rows, 16/2 heads, 387 -> 377; of 55
+// launches one lost more than 2 %, 2.3).  Launches of several layers gain where a
+// prompt has few tiles, so that the launch would end on the first prompt's long
+// ones alone (8 prompts, 4 layers, 8/8 heads, d = 64, 116 tiles a prompt: 39.3 ->
+// 36.4 us), and lose 3 to 13 % of the call from about 200 tiles a prompt on
+// (5 prompts of 663 rows, 4 layers, 16/2 heads, 216 a prompt: 61.5 -> 70.7 us; 3
+// of up to 1.3K rows, 32/4 heads, 752 a prompt: 155 -> 165): up to a quarter of
+// the resident workgroups (128) a prompt none of 11 lost.
+bool ordered(const AttnPlan& plan, AttnMode mode, int n_wg, int n_seqs, int n_layers) {
+  return mode == AttnMode::kWhole && n_seqs > 1 && n_seqs <= kOrderSeqs && plan.n_tiles > n_wg &&
+         (n_layers == 1 || plan.n_tiles <= (int64_t)n_seqs * (n_wg / 4));
 }
 
 // fp16 copy of the V cache of n_layers layers (status as for v16_kernel).
@@ -1693,7 +1703,7 @@ hipError_t launch_sparse_attn(const AttnPlan& plan, int n_layers, int n_q_heads,
   int n_wg = 0, n_first = 0;
   launch_shape(plan, &n_wg, &n_first);
   const AttnMode mode = attn_mode(plan, n_wg);
-  const bool order = ordered(plan, mode, n_wg, n_seqs);
+  const bool order = ordered(plan, mode, n_wg, n_seqs, n_layers);
   if (mode != AttnMode::kBalanced && !order) wplan = nullptr;
   launch_patch(n_layers, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs, rows, cu_rows,
                rows_per_layer, max_rows, k_fresh, v_fresh, k_cache, v_cache, plan, n_wg, n_first,
@@ -1726,7 +1736,7 @@ hipError_t launch_patch_layers(const AttnPlan& layer_plan, int n_layers, int n_k
   launch_shape(layer_plan, &n_wg, &n_first);
   // plans are needed (and built) only for balanced ranges and ordered tiles
   const AttnMode mode = attn_mode(layer_plan, n_wg);
-  const bool order = ordered(layer_plan, mode, n_wg, n_seqs);
+  const bool order = ordered(layer_plan, mode, n_wg, n_seqs, 1);
   int32_t* p = mode == AttnMode::kBalanced || order ? reinterpret_cast<int32_t*>(plans) : nullptr;
   if (max_rows > 0 || p != nullptr)
     launch_patch(n_layers, n_kv_heads, head_dim, t_total, cu_seqlens, n_seqs, rows, cu_rows,
@@ -1760,8 +1770,9 @@ hipError_t launch_sparse_attn_layer(const AttnPlan& layer_plan, int layer, int n
   launch_attend(layer_plan, n_wg, mode, n_q_heads, n_kv_heads, head_dim, t_total, cu_seqlens,
                 n_seqs, rows + set * t_total, cu_rows + set * (n_seqs + 1), 0, q + qo,
                 k_cache + kv, v_cache_f16 + kv, softmax_scale, out_dtype, out_l,
-                mode == AttnMode::kBalanced || ordered(layer_plan, mode, n_wg, n_seqs) ? wplan
-                                                                                       : nullptr,
+                mode == AttnMode::kBalanced || ordered(layer_plan, mode, n_wg, n_seqs, 1)
+                    ? wplan
+                    : nullptr,
                 parts, s);
   return hipGetLastError();
 }

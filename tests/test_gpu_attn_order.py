@@ -1,38 +1,47 @@
-"""GPU attention of batches whose tiles outnumber the resident workgroups: the
-launch then takes its tile slots in an order built on the device.  One tile more
-or fewer than the chip holds, prompts of one length and of falling and rising
-ones, empty prompts, one prompt more than the order takes, and row sets that
-differ between layers (the order comes from the first).  Against the float64
-oracle within |o - o_ref| <= 2e-2 + 1e-2 |o_ref|; rows outside the lists stay
-untouched.  Both the combined call and the per-layer calls."""
+"""GPU attention of batches whose tiles outnumber the resident workgroups (512
+on 256 CUs): launches of one layer, and those of several with at most 128 tiles a
+prompt, then take their tile slots in an order built on the device.  512 tiles (no
+order) and 516, prompts of one length and of falling and rising ones, empty
+prompts, one prompt more than the order takes, more slots than the builder
+handles in one round (1024; long tiles in both rounds), several layers with few
+and with many tiles a prompt, and row sets that differ between layers (the order
+comes from the first).  Against the float64 oracle within the bound of
+attn_check; rows outside the lists stay untouched.  Both the combined call, whose
+workspace shows whether an order was built and that it is a permutation, and the
+per-layer calls (which may take another launch shape)."""
 import sys
 
 import numpy as np
 import pytest
 import torch
 
+from attn_check import REL, worst_rel
 from oracle import attention as oatt
 from oracle import numerics
 
 pytestmark = pytest.mark.gpu
 
-CASES = [  # (prompt lengths, rows per prompt of layer 0, layers, q heads, kv heads, d)
-    ([300] * 2, [300] * 2, 8, 32, 8, 128),
-    ([700, 0, 300, 90, 33, 1], [700, 0, 300, 90, 33, 1], 2, 64, 2, 128),
-    ([40, 200, 500, 900], [40, 150, 500, 900], 1, 64, 4, 64),
-    ([64] * 64, [16] * 64, 1, 16, 8, 64),
-    ([64] * 65, [16] * 65, 1, 16, 8, 64),
+CASES = [  # (prompt lengths, rows per prompt of layer 0, layers, q heads, kv heads, d, ordered)
+    ([300] * 2, [300] * 2, 8, 32, 8, 128, False),                        # 672 tiles a prompt
+    ([700, 0, 300, 90, 33, 1], [700, 0, 300, 90, 33, 1], 2, 64, 2, 128, False),
+    ([200, 0, 150, 90] * 4, [200, 0, 150, 90] * 4, 2, 64, 2, 128, True),  # 114 a prompt
+    ([40, 200, 500, 900], [40, 150, 500, 900], 1, 64, 4, 64, True),
+    ([64] * 64, [16] * 64, 1, 16, 8, 64, True),
+    ([64] * 65, [16] * 65, 1, 16, 8, 64, False),
+    ([600, 408], [600, 408], 1, 64, 4, 64, False),                       # 4 x 128 tiles
+    ([608, 408], [608, 408], 1, 64, 4, 64, True),                        # 4 x 129
+    ([2000, 1500, 900, 900, 700], [2000, 1500, 900, 900, 700], 1, 64, 2, 64, True),  # 1500 slots with rows
 ]
 
 
 @pytest.mark.parametrize("c", CASES, ids=lambda c: "T%d_B%d_L%d_hq%d_hkv%d_d%d" % (
-    sum(c[0]), len(c[0]), *c[2:]))
+    sum(c[0]), len(c[0]), *c[2:6]))
 def test_attention_tile_order(c):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2608_21362_amd import kvb
 
-    lens, picks, L, hq, hkv, d = c
+    lens, picks, L, hq, hkv, d, ordered = c
     print(f"[attn-order] {sum(lens)} rows, {len(lens)} prompts, {L} layers, {hq}/{hkv} heads, d={d}",
           file=sys.stderr, flush=True)
     rng = np.random.default_rng(sum(lens) + hq)
@@ -72,6 +81,10 @@ def test_attention_tile_order(c):
         else:
             kvb.kvb_sparse_attn(L, hq, hkv, d, T, *args, q_d, k_d, v_d, kc, vc, v16, d ** -0.5,
                                 kvb.KVB_BF16, out, ws, need)
+            # the order of the slots follows the plan's four words
+            slots = -(-n_max // (128 * hkv // hq)) + B
+            order = ws[16:16 + 4 * slots].cpu().numpy().view(np.int32)
+            assert np.array_equal(np.sort(order), np.arange(slots) if ordered else np.full(slots, -1))
         torch.cuda.synchronize()
         outs.append(out.cpu().numpy())
     for l in range(L):
@@ -79,7 +92,8 @@ def test_attention_tile_order(c):
         ref = oatt.attend_rows(q[l], kf[l], vf[l], mine, cu)
         for out in outs:
             got = numerics.bf16_bits_to_f32(out.view(np.uint16)[l][mine]).astype(np.float64)
-            err = np.abs(got - ref)
-            assert np.all(err <= 2e-2 + 1e-2 * np.abs(ref)), (l, err.max())
+            err = worst_rel(got, ref)
+            print(f"[attn-order] layer {l}: worst relative error {err:.2e}", file=sys.stderr, flush=True)
+            assert err <= REL["bf16"], (l, err)
             others = np.setdiff1d(np.arange(T), mine)
             assert np.all(out[l][others] == -1), "a row outside the list was written"
