@@ -355,9 +355,10 @@ size_t kvb_sparse_attn_workspace_bytes(int32_t n_layers, int32_t n_q_heads, int3
  * as fp16 MFMA (probabilities and the copy of V in fp16), accumulation in
  * float.  Only rows of S_l are written in out (bf16 or f32 per out_dtype,
  * [L][t_total][Hq][d]).  max_rows bounds |S_l| and max_seq_len bounds T_b (host
- * values used to size the grid).  Deterministic: a tile's key ranges split
- * between workgroups are combined in key order.  Rows of S_l must be ascending
- * within each prompt and belong to it.
+ * values used to size the grid).  Deterministic: the sizes of the call decide
+ * how a row's keys are split; parts taken by several workgroups are combined in
+ * key order, parts taken by the waves of one in wave order.  Rows of S_l must
+ * be ascending within each prompt and belong to it.
  * Errors: KVB_EINVAL (incl. workspace too small, Hq % Hkv != 0),
  * KVB_EUNSUPPORTED (d not 64/128, Hq/Hkv not dividing 32). */
 kvb_status kvb_sparse_attn(int32_t n_layers, int32_t n_q_heads, int32_t n_kv_heads,
@@ -375,8 +376,13 @@ kvb_status kvb_sparse_attn(int32_t n_layers, int32_t n_q_heads, int32_t n_kv_hea
  * repair forward runs.  A caller that runs the repair forward layer by layer
  * can therefore patch every layer with one kvb_patch call right after the
  * selection, then make one kvb_sparse_attn_layer call per layer.  Results
- * (cache, fp16 copy of V, out) are bit-identical to kvb_sparse_attn over the
- * same rows. */
+ * (cache, fp16 copy of V, out) are bit-identical to one kvb_sparse_attn call
+ * per layer (n_layers = 1, the same sizes).  One kvb_sparse_attn call over
+ * several layers leaves the same cache and copy of V, but takes its launch
+ * shape from the tiles of all its layers: where that is another one than a
+ * layer's, a row's keys are added in another order, and out differs by the
+ * rounding of the fp16 probabilities (up to 1e-3 of a row's norm, before the
+ * output's own rounding). */
 
 /* Bytes of the plan buffer kvb_patch fills for n_layers layers (pure
  * function; 0 for invalid sizes).  The plans depend on the sizes given here and

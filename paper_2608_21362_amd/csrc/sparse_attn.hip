@@ -1553,9 +1553,15 @@ void launch_shape(const AttnPlan& plan, int* n_wg, int* n_first) {
 // ranges, whichever the estimate below says ends first (host arithmetic on the
 // call's sizes alone, so kvb_patch and kvb_sparse_attn_layer agree).  In
 // microseconds, fitted to 35 launches of 12 to 712 tiles over 128 to 8192 rows
-// (16 query heads, 2 kv heads, d = 128; other head shapes order the same way),
-// for which the choice is at most 7 % slower than the best shape and 1 % than
-// balanced ranges;
+// (16 query heads, 2 kv heads, d = 128), for which the choice is at most 7 %
+// slower than the best shape and 1 % than balanced ranges.  Not fitted to other
+// head shapes, but tried on them: per-layer calls of 128 to 5120 rows with 4/2 and
+// 8/8 heads at d = 64, 32/8, 32/4 and 32/1 at d = 128 take 0.47 to 1.00 of the time
+// of the rule before it (whole tiles up to 512 rows, balanced ranges above), none
+// of 35 longer.  All shapes count two resident workgroups per CU, also key-split
+// tiles at d = 64, of which a CU holds three.  A call over several layers is one
+// launch with all their tiles: 36 layers of 256 rows take whole tiles (39 us;
+// key-split 54), each by itself key-split ones.
 // b = key blocks of the longest prompt, w = tiles x b per resident workgroup,
 // r = tiles per resident workgroup:
 //  * whole tiles: a block takes 0.62 us of a workgroup alone on its CU and 0.92
