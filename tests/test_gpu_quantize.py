@@ -76,3 +76,47 @@ def test_quantise_bit_exact(s):
             assert np.array_equal(t[:, first:first + n_in], ref)
             rest = np.delete(t, np.s_[first:first + n_in], axis=1)
             assert np.all(rest == 77), "a layer outside the call was written"
+
+
+def _groups_ref(x, axis, bits):
+    """Codes, scale and zero of x f64 in groups along `axis`, for any values: a
+    minimum and maximum pass over NaN, and a quotient that is NaN gives code 0."""
+    levels = float((1 << bits) - 1)
+    mn = np.fmin.reduce(x, axis=axis, initial=np.inf, keepdims=True)
+    mx = np.fmax.reduce(x, axis=axis, initial=-np.inf, keepdims=True)
+    r = mx - mn
+    t = np.where(r != 0, (x - mn) / np.where(r != 0, r, 1) * levels, 0.0)
+    code = np.fmin(np.fmax(np.rint(t), 0.0), levels).astype(np.uint8)
+    return code, np.where(r == 0, 0, r / levels).astype(np.float32), mn.astype(np.float32)
+
+
+@pytest.mark.parametrize("bits,gk,gv,dt", [(4, 32, 16, np.float64), (8, 128, 64, np.float32), (8, 4, 32, np.float64)])
+@pytest.mark.filterwarnings("ignore::RuntimeWarning")
+def test_quantise_nan_and_infinities(bits, gk, gv, dt):
+    """Infinities and NaN, alone in a group, beside finite values and filling one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_21362_amd import kvb
+
+    print(f"[quantise] special values b{bits} k{gk} v{gv} {np.dtype(dt).name}", file=sys.stderr, flush=True)
+    P, d = 3, 64
+    rng = np.random.default_rng(bits + gk)
+    x = rng.standard_normal((2, P, 1, 1, 128, d)).astype(dt)
+    for p, special in enumerate((np.nan, np.inf, -np.inf)):
+        x[:, p][rng.random(x[:, p].shape) < 0.02] = special
+        x[:, p, 0, 0, :, 5] = x[:, p, 0, 0, 7, :] = special      # a whole channel, a whole token
+    k, v = x
+    pool = kvb.pool_layout(1, 1, d, bits, gk, gv)
+    new = lambda *shape, dtype: torch.zeros(shape, dtype=dtype, device="cuda")  # noqa: E731
+    kc, vc = (new(P, 1, 1, 128, d * bits // 8, dtype=torch.uint8) for _ in range(2))
+    ks, kz = (new(P, 1, 1, 128 // gk, d, dtype=torch.float32) for _ in range(2))
+    vs, vz = (new(P, 1, 1, 128, d // gv, dtype=torch.float32) for _ in range(2))
+    kvb.kvb_kivi_quantize(pool, P, 0, 1, kvb.KVB_F64 if dt == np.float64 else kvb.KVB_F32,
+                          torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda(), kc, ks, kz, vc, vs, vz)
+    torch.cuda.synchronize()
+    kg = _groups_ref(k.astype(np.float64).reshape(P, 1, 1, 128 // gk, gk, d), -2, bits)
+    vg = _groups_ref(v.astype(np.float64).reshape(P, 1, 1, 128, d // gv, gv), -1, bits)
+    for (code, scale, zero), (c, s, z) in ((kg, (kc, ks, kz)), (vg, (vc, vs, vz))):
+        assert np.array_equal(c.cpu().numpy(), kivi.pack(code.reshape(P, 1, 1, 128, d), bits))
+        for ref, t in ((scale, s), (zero, z)):
+            assert np.array_equal(t.cpu().numpy(), ref.reshape(t.shape), equal_nan=True)
