@@ -76,7 +76,7 @@ def test_trace_requests_match_the_oracle():
     """Two requests of a trace, run with the calls the trace times (fused
     stitch + deviation, selection, patch of every layer, one attention call
     per layer), against the oracle on the same draws: a short warm request
-    (3-4 chunks, whole-tile attention launch) and a long one (at least 20
+    (3-4 chunks, key-split attention tiles) and a long one (at least 20
     chunks, balanced ranges).  Stitch bit-exact, deviation within one float32 ulp,
     selection by the band rule, patch bit-exact on the GPU's rows, attention
     on every selected row of both layers within 2e-2 + 1e-2 |ref|."""
