@@ -384,6 +384,15 @@ __device__ __forceinline__ ImpSlot* imp_slot(int p, unsigned long long key) {
   return row + (__ffsll((unsigned long long)hit) - 1);
 }
 
+// x of the lane that a DPP control names (a vector move, no LDS round trip)
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+  const uint64_t w = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)w, CTRL, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(w >> 32), CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 // Sum of doubles that keeps the rounding errors of its additions (two-sum): about
 // 2^-104 relative, whatever the order.
 struct SumDD {
@@ -393,11 +402,16 @@ struct SumDD {
     c = (c + xc) + ((s - (t - y)) + (x - y));
     s = t;
   }
-  // sum over N adjacent lanes by a fixed xor tree (each ends with the same bits)
+  // sum over N adjacent lanes (16 or 64) by a fixed tree; each ends with the same
+  // bits.  Every lane must call.
   template <int N>
   __device__ __forceinline__ void add_lanes() {
+    add(dpp_f64<0xB1>(s), dpp_f64<0xB1>(c));    // quad_perm [1, 0, 3, 2]
+    add(dpp_f64<0x4E>(s), dpp_f64<0x4E>(c));    // quad_perm [2, 3, 0, 1]
+    add(dpp_f64<0x141>(s), dpp_f64<0x141>(c));  // row_half_mirror: the other quad of 8 lanes
+    add(dpp_f64<0x140>(s), dpp_f64<0x140>(c));  // row_mirror: the other 8 of 16
 #pragma unroll
-    for (int m = 1; m < N; m <<= 1) {
+    for (int m = 16; m < N; m <<= 1) {
       const double x = __shfl_xor(s, m, 64), xc = __shfl_xor(c, m, 64);
       add(x, xc);
     }
