@@ -10,7 +10,8 @@
 // output is ascending without a sort and no atomic decides an order.  LDS
 // atomics only count histogram bins.
 //
-// Segments of up to 64K rows use select_reg_kernel: the prompt's rows are split
+// Batches of up to 64K rows in all (a host value; the prompts' own lengths are on
+// the device) use select_reg_kernel: the prompt's rows are split
 // into 16 equal runs, one per wave, and lane i of a wave holds the keys and
 // flags of rows i, i + 64, .. of its run in registers (coalesced loads, read
 // once), so the histogram passes touch no memory but LDS and a row's rank is
@@ -24,7 +25,7 @@
 // with four 8-bit digits, one histogram and per-slot ranks through LDS), of
 // 32772 rows 22 us (65).  Adds to a spare word instead of a branch around rows
 // that do not count, and 16 copies of an 8-bit histogram, measured the same.
-// Longer segments use select_kernel, which re-reads the keys on every pass.
+// Larger batches use select_kernel, which re-reads the keys on every pass.
 //
 // Several prompts per set: rows go to a staging area at the prompt's own row
 // offset and a second small kernel packs them and writes cu_rows.
@@ -479,8 +480,9 @@ hipError_t launch_select(int32_t n_sets, int64_t t_total, const int32_t* cu_seql
     const size_t st = (size_t)n_sets * (size_t)t_total * sizeof(int32_t);
     counts = reinterpret_cast<int32_t*>(reinterpret_cast<char*>(workspace) + ((st + 255) / 256) * 256);
   }
-  // the longest prompt is at most t_total rows: pick the register-slot count
-  // from it (64 slots: the slot bits of a thread are one 64-bit word)
+  // the longest prompt is at most t_total rows: pick the register-slot count from
+  // it (at most 64 keys a thread: with 16 waves a workgroup a thread has 128
+  // registers)
   const dim3 grid(n_seqs, n_sets);
 #define KVB_SELECT_REG(K)                                                                       \
   hipLaunchKernelGGL(select_reg_kernel<K>, grid, dim3(kThreads), 0, s, t_total, cu_seqlens,     \

@@ -926,8 +926,8 @@ __device__ __forceinline__ void build_order(
 // its fp16 copy and, where selected, the cache's K and V.  The separate launches
 // cost a second launch and read the patched V rows back, but stream large caches
 // better: 36 layers of 8192 rows (151 MB of V) 71 us in two launches, 75 in one;
-// of 2432 rows (45 MB) 39 and 35; 4 layers of 1667 rows, d = 64 (1.7 MB) 6.6 and
-// 5.8 with a launch less.
+// of 2432 rows (45 MB) 39 and 36; 4 layers of 1667 rows, d = 64 (1.7 MB) 6.6 and
+// 5.4 with a launch less.
 constexpr int kFuseRows = 4096;
 constexpr int64_t kFuseBytes = 64 << 20;
 constexpr int kSpanMax = 64;
@@ -1192,10 +1192,12 @@ attn_kernel(int32_t balanced, int32_t n_tiles, int32_t Hq, int32_t Hkv, int32_t 
 // common maximum and added in wave order through LDS (the stages' space): no
 // partial records, no merge launch, and a chain of a quarter of the blocks.
 // The price is four times the block loads per query of a 128-query tile, so it
-// serves launches that leave the chip idle (attn_mode).  256 tokens, 163 rows:
-// 7.0 us against 11.7 for whole tiles; 1024 tokens, 777 rows: 15 us against 25
-// for balanced ranges and their merge.  Eight waves per tile measured 8.4 and
-// 20 us, two groups of queries sharing each wave pair's blocks 10 and 21 us.
+// serves launches that leave the chip idle (attn_mode).  Per-layer calls among
+// others: 256 tokens, 163 rows, 7.3 us against 11.8 for whole tiles; 1024 tokens,
+// 0.8K rows, 13.6 against 26.1 for balanced ranges and their merge; 2432 tokens,
+// 1.8K rows, 40.0 against 46.5.  Eight waves per tile took 8.4 and 20 us for the
+// launches of 256 and 1024 tokens where this form took 7.0 and 15, two groups of
+// queries sharing each wave pair's blocks 10 and 21.
 template <int D>
 __global__ void __launch_bounds__(kThreads, 2)
 attn_split_kernel(int32_t Hq, int32_t Hkv, int32_t log2g, int64_t t_total,
@@ -1556,7 +1558,7 @@ void launch_shape(const AttnPlan& plan, int* n_wg, int* n_first) {
 // (16 query heads, 2 kv heads, d = 128), for which the choice is at most 7 %
 // slower than the best shape and 1 % than balanced ranges.  Not fitted to other
 // head shapes, but tried on them: per-layer calls of 128 to 5120 rows with 4/2 and
-// 8/8 heads at d = 64, 32/8, 32/4 and 32/1 at d = 128 take 0.47 to 1.00 of the time
+// 8/8 heads at d = 64, 32/8, 32/4 and 32/1 at d = 128 take 0.49 to 1.00 of the time
 // of the rule before it (whole tiles up to 512 rows, balanced ranges above), none
 // of 35 longer.  All shapes count two resident workgroups per CU, also key-split
 // tiles at d = 64, of which a CU holds three.  A call over several layers is one

@@ -14,8 +14,8 @@
 // stitch_kernel requests every input before its key work starts, the head's key
 // statistics and the rotation row first: they are staged in LDS and read two
 // channel pairs at a time, widened to double once for the thread's four tokens.
-// (Held in registers for all 8 pairs they took 182 registers instead of 128, two
-// waves per SIMD instead of four: 32 int8 chunks x 36 layers 50.5 -> 49.2 us, 4.7
+// (Held in registers for all 8 pairs they took 182 registers instead of 120, two
+// waves per SIMD instead of four: 32 int8 chunks x 36 layers 51.0 -> 48.9 us, 4.7
 // TB/s from cold caches, where a streaming copy reaches 5.2.)
 // stitch_deviation_kernel, which also holds the fresh keys, reads the staged
 // statistics for every token and loads its value inputs after the key work:
