@@ -9,10 +9,10 @@ fp16 shadow and outputs bit for bit.  The per-layer ``kvb_sparse_attn`` path is
 checked against the oracle at these sizes elsewhere, and the small parity cases
 run the split path against the oracle directly.
 
-The cases cover both launch shapes of the attention kernel (balanced key
-ranges whose cut tiles are merged by the combine kernel, and one whole tile
-per workgroup, which the 32K workload takes), one row set shared by every
-layer, d = 64 with two query heads per kv head, a cold batch (every row live)
+The cases cover the launch shapes of the attention (balanced key ranges
+whose cut tiles are merged by the combine kernel, which the 8K workload takes,
+one whole tile per workgroup, which the 32K workload takes, and key-split tiles
+for the short prompts), one row set shared by every layer, d = 64 with two query heads per kv head, a cold batch (every row live)
 and a batch with no probed prompt.  A graph of the split step replays to the
 eager result.
 """
