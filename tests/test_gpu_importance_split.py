@@ -124,3 +124,40 @@ def test_importance_after_unordered_calls():
         np.testing.assert_allclose(out.cpu().numpy()[0], want, rtol=1e-12, atol=0)
         if n == L:
             assert out[0] == ref[0]
+
+
+def test_importance_graph_replays():
+    """Captured calls with chunks dealt to several workgroups, replayed one after
+    another and two graphs at once on two streams, give the eager bits."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2608_21362_amd import kvb
+
+    P, L, H, d = 6, 36, 1, 64
+    print("[importance-graph] 2 graphs", file=sys.stderr, flush=True)
+    pool = kvb.pool_layout(L, H, d, 8, 128, d)
+    g = torch.Generator("cuda").manual_seed(11)
+    keys = [torch.randn((P, L, H, 128, d), generator=g, device="cuda") for _ in range(2)]
+    outs = [torch.zeros(P, dtype=torch.float64, device="cuda") for _ in range(2)]
+    refs = [torch.zeros(P, dtype=torch.float64, device="cuda") for _ in range(2)]
+    for k, r in zip(keys, refs):
+        kvb.kvb_chunk_importance(pool, P, L, kvb.KVB_F32, k, r)
+    torch.cuda.synchronize()
+    graphs, streams = [], [torch.cuda.Stream(), torch.cuda.Stream()]
+    for k, o in zip(keys, outs):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            o.zero_()
+            kvb.kvb_chunk_importance(pool, P, L, kvb.KVB_F32, k, o)
+        graphs.append(graph)
+    torch.cuda.synchronize()
+    for r in range(5):
+        for graph, st in zip(graphs, streams):
+            with torch.cuda.stream(st):
+                for _ in range(1 + r):
+                    graph.replay()
+        torch.cuda.synchronize()
+        for o, ref in zip(outs, refs):
+            assert torch.equal(o, ref), r
+            o.fill_(-1.0)
+        torch.cuda.synchronize()
